@@ -384,14 +384,17 @@ typedef struct asv_tuning {
 int asv_verify_tuned(const asv_verify_args *args, const asv_tuning *tuning, void *workspace,
                      uint64_t workspace_bytes, void *stream);
 
-/* One launch of the LM-head kernel of asv_verify (see asv_k1_plan). */
+/* One launch of the LM-head kernel of asv_verify (see asv_k1_plan). Up to 64 rows the launch cuts
+ * its ids anew into narrower slabs, by V and the compute units (cut_rows64 in asv_api.hip); the
+ * fields then describe the uncut 256-id slabs. */
 typedef struct asv_k1_launch {
   int32_t tile_rows;              /* tree rows per workgroup tile: 64, 128, 192 or 256 */
   int32_t slab0;                  /* first vocabulary slab (256 ids each) of the launch */
   int32_t n_slabs;                /* slabs it covers */
   int32_t row_tiles;              /* tiles along the tree rows: ceil(N / tile_rows) */
-  int32_t k_loop;                 /* 0 burst ring, 1 one-slot ring, 2 two-slot spread loop,
-                                     3 three-slot spread loop */
+  int32_t k_loop;                 /* 2 two-slot spread loop, 3 three-slot spread loop; for
+                                     64-row tiles 0, or 1 when the tiles fit three workgroups
+                                     per compute unit but not two */
   int32_t stream_w;               /* 1: the weight is copied with the non-temporal hint */
   int32_t blk_slabs, blk_rows;    /* tile order: blocks of blk_slabs slabs x blk_rows row
                                      tiles, or 0 and 0 for the slab-major order */

@@ -22,8 +22,8 @@ namespace {
 
 constexpr size_t kAlign = 256;
 
-// Vocabulary rows per K1 workgroup tile = width of one record slab; every tile family below
-// uses this width, so the record layout depends only on V.
+// Vocabulary slabs of K1's plan. A launch beyond 64 rows runs one workgroup tile and writes one
+// record per slab and row; up to 64 rows the slabs are cut anew (cut_rows64).
 constexpr int kSlab = 256;
 constexpr int kPackRowsTarget = 256;   // rows per tile of the packed target LM-head weight
 constexpr int kPackRowsDraft = 64;     // rows per tile of the packed draft LM-head weight
@@ -139,11 +139,65 @@ void tile_blocking(int RT, int cus, int* blk_slabs, int* blk_rows) {
   }
 }
 
-// Whether a launch of `tiles` 64-row tiles runs the one-slot ring: its workgroups fit three
-// per CU but not two. Same-box A/Bs (K1, up to 64 rows): at V = 151936 (594 tiles on 256
-// CUs) 5.3% faster at 60 rows and 2.2% at 30; outside this range it was slower (V = 64000,
-// 250 tiles: +7%; V = 200000, 782 tiles: +6%) or level (V = 128256, 501 tiles).
-bool one_slot_64(int tiles, int cus) { return tiles > 2 * cus && tiles <= 3 * cus; }
+// Whether a launch of `tiles` 64-row tiles fits three workgroups per CU but not two (the plan's
+// k_loop; up to 64 rows cut_rows64 decides what runs).
+bool three_per_cu_64(int tiles, int cus) { return tiles > 2 * cus && tiles <= 3 * cus; }
+
+// ---- The cut of the vocabulary up to 64 rows, where K1 streams W once and nothing else counts.
+// 256-id slabs leave the chip short of work when there are few of them, and a short last round
+// when they do not divide among the CUs: V = 32000 gave 125 workgroups, V = 151936 two rounds of
+// which the second held 82. So the slabs are made as wide as an equal share of a CU's ids (one or
+// two workgroups per CU, every CU the same bytes) while that fits a tile, and beyond it 128-id
+// slabs fill whole rounds of two workgroups per CU and 64-id slabs share out the rest. Whole
+// verify steps at 60 rows and H = 4096, before -> after, packed weight (the floor is a 7.2 TB/s
+// read): V = 24000 80 -> 42 us (27), 32000 81 -> 48 (36), 40000 89 -> 58 (46), 64000 92 -> 83
+// (73), 80000 118 -> 102 (91), 140000 220 -> 176 (159), 151936 223 -> 196 (173), 200000 260 -> 250
+// (228); 100000 and 128256 are level.
+enum class Stream64 {
+  kDeep128,    // <= 128 ids, three slots, two workgroups per CU; the tail on 64 ids, four slots
+  kSpread256,  // <= 256 ids, one workgroup per CU, three-slot spread loop
+  kWide256,    // <= 256 ids, two slots, two workgroups per CU
+};
+
+struct Cut64 {
+  Stream64 kind;
+  SlabCut cut;
+  int S;         // slabs in all = records per row
+  bool tail64;   // the tail's slabs hold at most 64 ids: they run on the 64-id tile
+};
+
+// Narrower slabs than this cost more in X copies and records than they share out.
+constexpr int kMinCut = 32;
+// Vocabularies beyond this keep 256-id slabs: at two workgroups per CU their last round is a
+// small part of the launch, and their records stay as few as they were.
+constexpr int kMaxCutVocab = 1 << 18;
+
+Cut64 cut_rows64(int V, int cus) {
+  // ids per slab when n slabs share `ids`, in whole groups of 8
+  auto share = [](int ids, int n) { return std::max(kMinCut, ((ids + n - 1) / n + 7) / 8 * 8); };
+  auto even = [&](Stream64 kind, int width) {
+    const int S = (V + width - 1) / width;
+    return Cut64{kind, SlabCut{S, width, width, 0, 0}, S, false};
+  };
+  if (V > kMaxCutVocab) return even(Stream64::kWide256, kSlab);
+  const int one = share(V, cus), two = share(V, 2 * cus);
+  if (one <= 128) return even(Stream64::kDeep128, one);
+  // one workgroup per CU is 4-7% ahead of two half as wide at 150-200 ids (V = 40000: 57 against
+  // 62 us, 50000: 68-70 against 71-73) and 2% behind at 250 (V = 64000: 85 against 83)
+  if (one <= 224) return even(Stream64::kSpread256, one);
+  if (two <= 128) return even(Stream64::kDeep128, two);
+  if (two <= 256) return even(Stream64::kWide256, two);
+  const int n1 = V / (2 * cus * 128) * 2 * cus, rest = V - n1 * 128;
+  const bool tail64 = rest <= 2 * cus * 64;
+  const int tw = tail64 ? 64 : share(rest, 2 * cus);
+  return Cut64{Stream64::kDeep128, SlabCut{n1, 128, tw, 0, 0}, n1 + (rest + tw - 1) / tw, tail64};
+}
+
+// Most records per row that a step of N rows writes, whatever the device's CU count.
+int max_records(int N, int V) {
+  const int width = N <= 64 && V <= kMaxCutVocab ? kMinCut : kSlab;
+  return (V + width - 1) / width;
+}
 
 // Launches of at most this many row tiles copy W with the non-temporal hint (the one or two
 // tiles of a slab read it about once); more row tiles share each W slab through an XCD's L2
@@ -173,7 +227,7 @@ int k1_launches(int N, int S, int cus, const K1Plan& plan, asv_k1_launch out[2])
     k.row_tiles = (N + k.tile_rows - 1) / k.tile_rows;
     const int tiles = n_slabs * k.row_tiles;
     switch (t) {
-      case Tile::kRows64: k.k_loop = one_slot_64(tiles, cus) ? 1 : 0; break;
+      case Tile::kRows64: k.k_loop = three_per_cu_64(tiles, cus) ? 1 : 0; break;
       case Tile::kRows128: k.k_loop = 3; break;
       default: k.k_loop = 2; break;
     }
@@ -197,7 +251,7 @@ bool forced_tile(int rows, Tile* t) {
 }
 
 struct Layout {
-  int S = 0;       // vocabulary slabs
+  int S = 0;       // vocabulary slabs of the plan
   int n_conf = 0;  // draft-confidence chunks per request
   size_t off_rec_m = 0, off_rec_s = 0, off_rec_a = 0, off_conf_m = 0, off_conf_s = 0;
   size_t off_cnt = 0;  // B + 1 ints: per-request completion counters, then the bad-offsets flag
@@ -208,7 +262,7 @@ Layout layout(int B, int N, int V) {
   Layout L;
   L.S = (V + kSlab - 1) / kSlab;
   L.n_conf = (V + kConfChunk - 1) / kConfChunk;
-  const size_t rec = (size_t)N * L.S * 4;
+  const size_t rec = (size_t)N * max_records(N, V) * 4;
   const size_t conf = (size_t)B * L.n_conf * 4;
   size_t at = 0;
   L.off_rec_m = at;  at += align_up(rec);
@@ -249,7 +303,6 @@ bool params_ok(const asv_params& p) {
   return true;
 }
 
-// K1 over the vocabulary slabs [slab0, slab0 + n_slabs).
 // Launches `kernel` on `s`; with a start or stop event (measurement only) through
 // hipExtLaunchKernelGGL, which sets the events to the dispatch's own start and end times.
 template <typename F, typename... Args>
@@ -261,25 +314,72 @@ void launch_timed(F kernel, int grid, int threads, hipStream_t s, hipEvent_t sta
     kernel<<<grid, threads, 0, s>>>(args...);
 }
 
-template <int TV, int TR, int WV, int WR, int BK, int NST, int LOOP>
-void launch_lmhead(const asv_verify_args* a, const Layout& L, char* ws, hipStream_t s,
-                   const asv_k1_launch& k, hipEvent_t start, hipEvent_t stop) {
-  static_assert(TV == kSlab, "tiles span exactly one record slab");
-  static_assert(TV == kPackRowsTarget && BK == kPackDepth, "a stage is one packed tile");
-  const int grid = k.n_slabs * k.row_tiles;
-  auto go = [&](auto kernel) {
-    launch_timed(kernel, grid, WV * WR * kWave, s, start, stop, a->hidden, a->w_lm, a->parent,
-                 a->draft_tok, a->req_offsets, a->B, a->N, a->H, a->V, L.S, k.slab0,
-                 k.row_tiles, reinterpret_cast<float*>(ws + L.off_rec_m),
-                 reinterpret_cast<float*>(ws + L.off_rec_s),
-                 reinterpret_cast<int32_t*>(ws + L.off_rec_a), a->drafted_logit,
-                 reinterpret_cast<int32_t*>(ws + L.off_cnt), a->B + 1,
-                 a->w_lm_layout == ASV_W_PACKED ? 1 : 0, k.blk_slabs, k.blk_rows);
-  };
+LmheadArgs lmhead_args(const asv_verify_args* a, const Layout& L, char* ws, int S) {
+  LmheadArgs r;
+  r.X = a->hidden;
+  r.W = a->w_lm;
+  r.parent = a->parent;
+  r.draft_tok = a->draft_tok;
+  r.req_offsets = a->req_offsets;
+  r.B = a->B;
+  r.N = a->N;
+  r.H = a->H;
+  r.V = a->V;
+  r.S = S;
+  r.rec_m = reinterpret_cast<float*>(ws + L.off_rec_m);
+  r.rec_s = reinterpret_cast<float*>(ws + L.off_rec_s);
+  r.rec_a = reinterpret_cast<int32_t*>(ws + L.off_rec_a);
+  r.drafted_logit = a->drafted_logit;
+  r.done_cnt = reinterpret_cast<int32_t*>(ws + L.off_cnt);
+  r.n_cnt = a->B + 1;
+  r.w_packed = a->w_lm_layout == ASV_W_PACKED ? kPackRowsTarget : 0;
+  return r;
+}
+
+struct K1Events {
+  hipEvent_t start, stop;
+};
+
+// The tiles of `cut` (n_tail slabs in its tail) x k.row_tiles on families M and T.
+template <class M, class T = M>
+void launch_lmhead(const LmheadArgs& g, const SlabCut& cut, int n_tail, const asv_k1_launch& k,
+                   hipStream_t s, const K1Events& ev) {
+  static_assert(M::BK == kPackDepth, "a stage is one packed column block");
+  launch_timed(k_lmhead_partial<M, T>, cut.n_main * k.row_tiles + n_tail, M::C::kThreads, s,
+               ev.start, ev.stop, g, cut, k.row_tiles, k.blk_slabs, k.blk_rows);
+}
+
+// One launch of the plan over whole 256-id slabs.
+template <int TR, int WV, int WR, int NST, int LOOP>
+void launch_slabs(const LmheadArgs& g, const asv_k1_launch& k, hipStream_t s,
+                  const K1Events& ev) {
+  const SlabCut cut{k.n_slabs, kSlab, kSlab, k.slab0, k.slab0 * kSlab};
   if (k.stream_w)
-    go(k_lmhead_partial<TV, TR, WV, WR, BK, NST, LOOP, true>);
+    launch_lmhead<TileFamily<kSlab, TR, WV, WR, NST, LOOP, true>>(g, cut, 0, k, s, ev);
   else
-    go(k_lmhead_partial<TV, TR, WV, WR, BK, NST, LOOP, false>);
+    launch_lmhead<TileFamily<kSlab, TR, WV, WR, NST, LOOP, false>>(g, cut, 0, k, s, ev);
+}
+
+// Up to 64 rows: one launch over the slabs of cut_rows64.
+void launch_rows64(const LmheadArgs& g, const Cut64& c, const asv_k1_launch& k, hipStream_t s,
+                   const K1Events& ev) {
+  using Deep128 = TileFamily<128, 64, 4, 1, 3, 0, true>;
+  using Deep64 = TileFamily<64, 64, 4, 1, 4, 0, true>;
+  const int n_tail = c.S - c.cut.n_main;
+  switch (c.kind) {
+    case Stream64::kDeep128:
+      if (c.tail64)
+        launch_lmhead<Deep128, Deep64>(g, c.cut, n_tail, k, s, ev);
+      else
+        launch_lmhead<Deep128>(g, c.cut, n_tail, k, s, ev);
+      break;
+    case Stream64::kSpread256:
+      launch_lmhead<TileFamily<256, 64, 2, 2, 3, 3, true>>(g, c.cut, n_tail, k, s, ev);
+      break;
+    case Stream64::kWide256:
+      launch_lmhead<TileFamily<256, 64, 4, 1, 2, 0, true>>(g, c.cut, n_tail, k, s, ev);
+      break;
+  }
 }
 
 // Total bytes of the packed copy of a [V][H] weight whose K blocks hold V rounded up to
@@ -394,7 +494,7 @@ void launch_draft(const asv_draft_args* a, const DraftLayout& L, char* ws, hipSt
   const int RT = (R + TR - 1) / TR;
   launch_timed(k_draft_partial<TV, TR, WV, WR, BK, NST>, L.S * RT, WV * WR * kWave, s, start, stop,
       a->hidden, a->w_draft, R, a->H, a->V, L.S, RT, reinterpret_cast<uint64_t*>(ws + L.off_k),
-      reinterpret_cast<float*>(ws + L.off_s), a->w_draft_layout == ASV_W_PACKED ? 1 : 0);
+      reinterpret_cast<float*>(ws + L.off_s), a->w_draft_layout == ASV_W_PACKED ? 128 : 0);
 }
 
 // ---- static scratch of asv_verify_noalloc
@@ -517,35 +617,35 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
     if (int rc = launch_status("k_draft_conf_partial")) return rc;
   }
 
+  const int cus = cu_count();
   const K1Plan plan = tu.tile_rows != 0 ? K1Plan{forced, forced, L.S}
-                                         : plan_k1(a->N, L.S, cu_count());
+                                         : plan_k1(a->N, L.S, cus);
   asv_k1_launch k1[2];
-  const int n_k1 = k1_launches(a->N, L.S, cu_count(), plan, k1);
+  const int n_k1 = k1_launches(a->N, L.S, cus, plan, k1);
+  const bool rows64 = k1[0].tile_rows == 64 && a->N <= 64;
+  const Cut64 cut64 = cut_rows64(a->V, cus);
+  const int S = rows64 ? cut64.S : L.S;             // records per row
+  const LmheadArgs g = lmhead_args(a, L, ws, S);
   // timing events (measurement only): the start of the first launch, the end of the last
   const hipEvent_t ev_begin = reinterpret_cast<hipEvent_t>(tu.begin_event);
   const hipEvent_t ev_end = reinterpret_cast<hipEvent_t>(tu.end_event);
   for (int q = 0; q < n_k1; ++q) {
     const asv_k1_launch& k = k1[q];
-    const hipEvent_t start = q == 0 ? ev_begin : nullptr;
-    const hipEvent_t stop = q == n_k1 - 1 ? ev_end : nullptr;
-    // <vocab rows, tree rows, waves along vocab, waves along rows, K per stage, ring depth,
-    // K loop>, each the fastest of a sweep on MI355X for its row range. The weight-streaming
-    // 64-row tile keeps two workgroups per CU (80 KB of LDS each) with the burst ring, or
-    // three (40 KB each) with the one-slot ring when that takes every tile at once; a 3-deep
-    // ring with one workgroup per CU was 0.7% slower in an interleaved comparison over ten
-    // placements of W. The 128-, 192- and 256-row tiles run the spread K loops (copies spaced
-    // between the MFMAs), in interleaved comparisons 28% faster than the burst ring at 378
-    // rows and 20% at 2048 and 3048 rows.
+    const K1Events ev{q == 0 ? ev_begin : nullptr, q == n_k1 - 1 ? ev_end : nullptr};
+    // <tree rows, waves along vocab, waves along rows, ring depth, K loop>, each the fastest of
+    // a sweep on MI355X for its row range. The 128-, 192- and 256-row tiles run the spread K
+    // loops (copies spaced between the MFMAs), in interleaved comparisons 28% faster than the
+    // burst ring at 378 rows and 20% at 2048 and 3048 rows.
     switch (k.tile_rows) {
       case 64:
-        if (k.k_loop == 1)
-          launch_lmhead<256, 64, 4, 1, 64, 1, 1>(a, L, ws, s, k, start, stop);
+        if (rows64)
+          launch_rows64(g, cut64, k, s, ev);
         else
-          launch_lmhead<256, 64, 4, 1, 64, 2, 0>(a, L, ws, s, k, start, stop);
+          launch_slabs<64, 4, 1, 2, 0>(g, k, s, ev);
         break;
-      case 128: launch_lmhead<256, 128, 2, 2, 64, 3, 3>(a, L, ws, s, k, start, stop); break;
-      case 192: launch_lmhead<256, 192, 2, 2, 64, 2, 2>(a, L, ws, s, k, start, stop); break;
-      default: launch_lmhead<256, 256, 2, 2, 64, 2, 2>(a, L, ws, s, k, start, stop); break;
+      case 128: launch_slabs<128, 2, 2, 3, 3>(g, k, s, ev); break;
+      case 192: launch_slabs<192, 2, 2, 2, 2>(g, k, s, ev); break;
+      default: launch_slabs<256, 2, 2, 2, 2>(g, k, s, ev); break;
     }
   }
   if (int rc = launch_status("k_lmhead_partial")) return rc;
@@ -557,12 +657,12 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   int32_t* cnt = reinterpret_cast<int32_t*>(ws + L.off_cnt);
   if (a->B <= kFusedMaxB) {
     k_merge_accept<<<(a->N + kFinishWaves - 1) / kFinishWaves, kFinishWaves * kWave, 0, s>>>(
-        L.S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, cnt, acc);
+        S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, cnt, acc);
     return launch_status("k_merge_accept");
   }
   k_slab_merge<<<(a->N + kMergeRowsPerBlock - 1) / kMergeRowsPerBlock,
                  kMergeRowsPerBlock * kWave, 0, s>>>(
-      a->N, L.S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, a->B,
+      a->N, S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, a->B,
       a->req_offsets, cnt + a->B);
   if (int rc = launch_status("k_slab_merge")) return rc;
   k_tree_accept<<<a->B, kWave, 0, s>>>(cnt + a->B, acc);

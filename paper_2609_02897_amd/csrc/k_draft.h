@@ -180,7 +180,8 @@ void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict_
   // The non-temporal hint on the W copies pays for tiles of up to 64 rows (4 rows: 5% less
   // time after a cache flush); the 128-row tile is faster without it, because the draft
   // weight (262 MB at 32000 ids) largely fits the last-level cache.
-  lmhead_tile<TV, TR, WV, WR, BK, NST, (TR <= 64)>(X, W, R, H, V, v0, r0, smem, w_packed, acc);
+  lmhead_tile<TV, TR, WV, WR, BK, NST, (TR <= 64)>(X, W, R, H, V, v0, min(v0 + TV, V), r0,
+                                                  smem, w_packed, acc);
 
   // Output block (i, j), register e of a lane holds vocabulary row
   //   v0 + wv * kWaveV + 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4   and

@@ -171,14 +171,20 @@ struct LmheadCfg {
   static constexpr int kLoads = DW + DX;        // vector-memory ops per lane per stage
   static constexpr int kLds = NST * kStage;
   static constexpr int kCand = 2;               // gather candidates prefetched per thread
+  // K1's epilogue scratch, which reuses the ring: the gather list (kCap entries of 16 bytes), one
+  // 64 x kRegs-float extraction area per wave, the row-reduction exchange and two counters.
+  static constexpr int kCap = 1024;
+  static constexpr int kScrOff = kCap * 16;
+  static constexpr int kRedOff = kScrOff + kWaves * kWave * MF::kRegs * 4;
+  static constexpr int kCntOff = kRedOff + 3 * WV * TR * 4;
   static_assert(TV % 32 == 0 && TR % 32 == 0 && kWaveV % MF::kBlock == 0 &&
                 kWaveR % MF::kBlock == 0, "whole MFMA blocks");
   static_assert(MV >= 1 && MR >= 1, "tile too small for the wave grid");
   static_assert(BK == 32 || BK == 64, "stage depth");
-  static_assert(NST >= 1 && NST <= 5, "ring depth");
+  static_assert(NST >= 2 && NST <= 5, "ring depth");
   static_assert(DW >= 1 && DX >= 1 && DW * kWaves * 1024 == kStageW &&
                 DX * kWaves * 1024 == kStageX, "each wave copies whole 1 KB groups");
-  static_assert(NST < 2 || (NST - 2) * kLoads <= 63, "vmcnt range");
+  static_assert((NST - 2) * kLoads <= 63, "vmcnt range");
   static_assert(kLds <= 160 * 1024, "LDS per workgroup");
 };
 
@@ -227,10 +233,14 @@ __host__ __device__ __forceinline__ void tile_coords(int t, int n_slabs, int RT,
 // (R = kRowsPerCopy): lane t supplies 16 bytes of row R j + t / CPR at swizzled position
 // t % CPR, i.e. the logical chunk (t % CPR) ^ f(R j + t / CPR).
 // W is row-major [V][H], or packed (w_packed != 0, written by k_pack_tiles with BK = 64):
-// K block k holds rows 0 .. Vp - 1 (V rounded up to max(TV, 128) rows, zero past V) as
-// consecutive [BK]-wide row segments, so the TV rows of slab s at K block k are one contiguous
+// K block k holds rows 0 .. Vp - 1 (V rounded up to w_packed rows, zero past V) as
+// consecutive [BK]-wide row segments, so the rows of a tile at K block k are one contiguous
 // run starting at element k Vp BK + v0 BK. Offsets within the packed buffer are 32-bit
 // unsigned (the host keeps it under 4 GiB).
+// The tile's vocabulary rows are v0 .. v_end - 1, at most TV of them; the caller discards the
+// results of the others. Their copies read nothing: the row-major resource ends at v_end, and in
+// the packed weight, whose rows past v_end belong to the next tile, their offset is set past any
+// buffer of up to 2 GiB (in a larger one those rows are read and discarded).
 // STREAM_W: copy W with the non-temporal hint. K1 takes it for launches of one or two row
 // tiles, which read each W slab about once (60 rows: 13% less time), and the default policy
 // for more row tiles, which share each W slab through an XCD's L2 (with the hint: 378 rows'
@@ -254,7 +264,8 @@ struct TileIo {
   int w_voff[C::DW], x_voff[C::DX];
 
   __device__ __forceinline__ TileIo(const uint16_t* X, const uint16_t* W, int N, int H, int V,
-                                    int v0, int r0, const uint4* smem, int w_packed)
+                                    int v0, int v_end, int r0, const uint4* smem,
+                                    int w_packed)
       : lds(smem) {
     lane = threadIdx.x & 63;
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -271,15 +282,16 @@ struct TileIo {
           C::kStageW / 16 + swz<CPR>(wr * C::kWaveR + frag_row, (MF::kK / 8) * s + frag_grp);
     }
     lds0 = __builtin_amdgcn_readfirstlane((int)(size_t)smem);
-    const int v_end = min(v0 + TV, V);
     const int r_last = min(r0 + TR, N) - 1;
+    int w_rows = TV;                // rows whose copies keep their offset
     if (w_packed) {
-      constexpr unsigned kAlign = TV > 128 ? TV : 128;
-      const unsigned Vp = (V + kAlign - 1) / kAlign * kAlign, tile = TV * BK * 2;
+      const unsigned align = w_packed, Vp = (V + align - 1) / align * align;
       w_kstep = Vp * BK * 2;
       w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
           const_cast<uint16_t*>(W + (size_t)v0 * BK), (short)0,
-          (int)((unsigned)(H / BK - 1) * w_kstep + tile), kRsrcWord3);
+          (int)((unsigned)(H / BK - 1) * w_kstep + min((unsigned)TV, Vp - v0) * BK * 2),
+          kRsrcWord3);
+      if ((unsigned)(H / BK) * w_kstep <= 0x80000000u) w_rows = v_end - v0;
     } else {
       w_kstep = BK * 2;
       w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(W + (size_t)v0 * H),
@@ -288,8 +300,11 @@ struct TileIo {
     x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(X + (size_t)r0 * H),
                                                (short)0, (r_last + 1 - r0) * H * 2, kRsrcWord3);
 #pragma unroll
-    for (int i = 0; i < C::DW; ++i)
-      w_voff[i] = copy_voff(i * C::kWaves + wave, w_packed ? BK : H);
+    for (int i = 0; i < C::DW; ++i) {
+      const int j = i * C::kWaves + wave;
+      w_voff[i] = j * C::kRowsPerCopy + lane / CPR < w_rows ? copy_voff(j, w_packed ? BK : H)
+                                                            : (int)0x80000000;
+    }
 #pragma unroll
     for (int i = 0; i < C::DX; ++i) x_voff[i] = copy_voff(i * C::kWaves + wave, H);
   }
@@ -346,11 +361,12 @@ template <int TV, int TR, int WV, int WR, int BK, int NST, bool STREAM_W = (TR <
           class MF = Mfma32>
 __device__ __forceinline__ void lmhead_tile(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
-    int v0, int r0, uint4* smem, int w_packed,
+    int v0, int v_end, int r0, uint4* smem, int w_packed,
     typename MF::Acc (&acc)[LmheadCfg<TV, TR, WV, WR, BK, NST, MF>::MV]
                            [LmheadCfg<TV, TR, WV, WR, BK, NST, MF>::MR]) {
   using C = LmheadCfg<TV, TR, WV, WR, BK, NST, MF>;
-  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, r0, smem, w_packed);
+  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, v_end, r0, smem,
+                                                         w_packed);
   const int KT = H / BK;
   auto issue_stage = [&](int ks) {
     static_for<C::kLoads>([&](auto cc) { io.template copy<decltype(cc)::value>(ks % NST, ks); });
@@ -412,48 +428,6 @@ __device__ __forceinline__ void wait_lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
 }
 
-// The same logits as lmhead_tile with a one-slot ring, for weight-streaming tiles that run
-// three workgroups per CU: each wave reads a whole stage's fragments into registers, the
-// workgroup frees the slot and refills it with the next stage while this stage's MFMAs run.
-// A stage's copy latency is exposed per workgroup and hidden by the other workgroups of the
-// CU. MFMAs accumulate in lmhead_tile's K order, so the logits are bit-identical.
-template <int TV, int TR, int WV, int WR, int BK, bool STREAM_W, class MF>
-__device__ __forceinline__ void lmhead_tile_1slot(
-    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
-    int v0, int r0, uint4* smem, int w_packed,
-    typename MF::Acc (&acc)[LmheadCfg<TV, TR, WV, WR, BK, 1, MF>::MV]
-                           [LmheadCfg<TV, TR, WV, WR, BK, 1, MF>::MR]) {
-  using C = LmheadCfg<TV, TR, WV, WR, BK, 1, MF>;
-  const TileIo<TV, TR, WV, WR, BK, 1, STREAM_W, MF> io(X, W, N, H, V, v0, r0, smem, w_packed);
-  const int KT = H / BK;
-  auto issue_stage = [&](int ks) {
-    static_for<C::kLoads>([&](auto cc) { io.template copy<decltype(cc)::value>(0, ks); });
-  };
-  zero_acc(acc);
-  constexpr int NS = C::NS;
-  bf16x8 fa[NS][C::MV], fb[NS][C::MR];
-  issue_stage(0);
-  for (int k = 0; k < KT; ++k) {
-    wait_vm_barrier<0>();                 // stage k has landed in the slot
-#pragma unroll
-    for (int s = 0; s < NS; ++s) {
-#pragma unroll
-      for (int i = 0; i < C::MV; ++i) fa[s][i] = io.w_frag(0, s, i);
-#pragma unroll
-      for (int j = 0; j < C::MR; ++j) fb[s][j] = io.x_frag(0, s, j);
-    }
-    wait_lds_barrier();                   // every wave holds its fragments: the slot is free
-    if (k + 1 < KT) issue_stage(k + 1);
-#pragma unroll
-    for (int s = 0; s < NS; ++s)
-#pragma unroll
-      for (int i = 0; i < C::MV; ++i)
-#pragma unroll
-        for (int j = 0; j < C::MR; ++j) acc[i][j] = MF::mma(fa[s][i], fb[s][j], acc[i][j]);
-  }
-  __syncthreads();
-}
-
 // The same logits as lmhead_tile for 64-deep stages in a two-slot ring, with a fixed
 // instruction schedule that spreads each stage's copies over the MFMAs. A stage has NS MFMA K
 // steps (four K16 steps of 32x32x16, or two K32 steps of 16x16x32) of NF = MV + MR fragments
@@ -475,7 +449,7 @@ __device__ __forceinline__ void lmhead_tile_1slot(
 template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma32>
 __device__ __forceinline__ void lmhead_tile_spread(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
-    int v0, int r0, uint4* smem, int w_packed,
+    int v0, int v_end, int r0, uint4* smem, int w_packed,
     typename MF::Acc (&acc)[LmheadCfg<TV, TR, WV, WR, 64, 2, MF>::MV]
                            [LmheadCfg<TV, TR, WV, WR, 64, 2, MF>::MR]) {
   constexpr int BK = 64, NST = 2;
@@ -501,7 +475,7 @@ __device__ __forceinline__ void lmhead_tile_spread(
     return n;
   }();
 
-  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, r0, smem,
+  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, v_end, r0, smem,
                                                         w_packed);
   const int KT = H / BK;
   auto issue_copy = [&](int slot, int ks, auto cc) {
@@ -578,7 +552,7 @@ __device__ __forceinline__ void lmhead_tile_spread(
 template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma32>
 __device__ __forceinline__ void lmhead_tile_spread3(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
-    int v0, int r0, uint4* smem, int w_packed,
+    int v0, int v_end, int r0, uint4* smem, int w_packed,
     typename MF::Acc (&acc)[LmheadCfg<TV, TR, WV, WR, 64, 3, MF>::MV]
                            [LmheadCfg<TV, TR, WV, WR, 64, 3, MF>::MR]) {
   constexpr int BK = 64, NST = 3;
@@ -602,7 +576,7 @@ __device__ __forceinline__ void lmhead_tile_spread3(
     return n;
   }();
 
-  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, r0, smem,
+  const TileIo<TV, TR, WV, WR, BK, NST, STREAM_W, MF> io(X, W, N, H, V, v0, v_end, r0, smem,
                                                         w_packed);
   const int KT = H / BK;
   // copy c of stage j into slot j % 3, from K stage min(j, KT - 1)
@@ -655,41 +629,68 @@ __device__ __forceinline__ void lmhead_tile_spread3(
   __syncthreads();
 }
 
-// LOOP selects the K loop: 0 = the burst ring of lmhead_tile; 1 = the one-slot ring of
-// lmhead_tile_1slot (three workgroups per CU); 2 and 3 = the spread loop of that ring depth
-// (lmhead_tile_spread, lmhead_tile_spread3). STREAM_W: the W copies' cache
-// policy (see TileIo); it changes no result. MF is the MFMA shape; every tile
-// family of K1 runs the same one, so that all of them sum each logit's products in the same
-// order and give the same logits bit for bit. One launch covers a contiguous range of
-// vocabulary slabs (all of them, or one of two ranges whose tiles differ in height).
-template <int TV, int TR, int WV, int WR, int BK, int NST, int LOOP, bool STREAM_W,
-          class MF = Mfma16>
-__global__ __launch_bounds__(WV * WR * kWave, LOOP == 1 ? 3 : 1)
-void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
-                      const int32_t* __restrict__ parent, const int32_t* __restrict__ draft_tok,
-                      const int32_t* __restrict__ req_offsets, int B, int N, int H, int V,
-                      int S, int slab0, int RT, float* __restrict__ rec_m,
-                      float* __restrict__ rec_s, int32_t* __restrict__ rec_a,
-                      float* __restrict__ drafted_logit, int32_t* __restrict__ done_cnt,
-                      int n_cnt, int w_packed, int blk_slabs, int blk_rows) {
+// Arguments of a K1 launch that its tiles share.
+struct LmheadArgs {
+  const uint16_t* X;
+  const uint16_t* W;
+  const int32_t* parent;
+  const int32_t* draft_tok;
+  const int32_t* req_offsets;
+  int B, N, H, V;
+  int S;                         // records per tree row over all launches of the step
+  float* rec_m;
+  float* rec_s;
+  int32_t* rec_a;
+  float* drafted_logit;
+  int32_t* done_cnt;             // n_cnt counters of the finishing kernel, cleared here
+  int n_cnt;
+  int w_packed;                  // 0: W row-major; else packed, V rounded up to this many rows
+};
+
+// How a launch cuts the vocabulary into the tiles' slabs: slabs [0, n_main) of `width` ids, then
+// slabs of tail_width ids up to the last id. Slab k of the launch has record slab0 + k and its
+// ids start at v_first + k width (v_first + n_main width + (k - n_main) tail_width in the tail).
+struct SlabCut {
+  int n_main, width, tail_width;
+  int slab0, v_first;
+};
+
+// A tile family. LOOP selects the K loop: 0 = the burst ring of lmhead_tile; 2 and 3 = the spread
+// loop of that ring depth (lmhead_tile_spread, lmhead_tile_spread3). STREAM_W: the W copies'
+// cache policy (see TileIo); it changes no result. MF is the MFMA shape; every tile family of K1
+// runs the same one, so that all of them sum each logit's products in the same order and give
+// the same logits bit for bit.
+template <int TV_, int TR_, int WV_, int WR_, int NST_, int LOOP_, bool STREAM_W_>
+struct TileFamily {
+  static constexpr int TV = TV_, TR = TR_, WV = WV_, WR = WR_, BK = 64, NST = NST_, LOOP = LOOP_;
+  static constexpr bool STREAM_W = STREAM_W_;
+  using MF = Mfma16;
   using C = LmheadCfg<TV, TR, WV, WR, BK, NST, MF>;
+  static_assert(C::kCntOff + 8 <= C::kLds, "epilogue scratch exceeds the LDS ring");
+};
+
+// One tile: ids v0 .. v_end - 1 (at most TV), tree rows r0 .. r0 + TR - 1; `rec` is the record
+// each of its rows writes.
+template <class F>
+__device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_end, int r0,
+                                             int rec, uint4* smem) {
+  constexpr int TV = F::TV, TR = F::TR, WV = F::WV, WR = F::WR, BK = F::BK, NST = F::NST;
+  constexpr bool STREAM_W = F::STREAM_W;
+  using MF = typename F::MF;
+  using C = typename F::C;
   constexpr int T = C::kThreads;
   constexpr int kBlock = MF::kBlock, kRegs = MF::kRegs;
-  __shared__ uint4 smem[C::kLds / 16];
+  const uint16_t* __restrict__ X = a.X;
+  const uint16_t* __restrict__ W = a.W;
+  const int32_t* __restrict__ parent = a.parent;
+  const int32_t* __restrict__ draft_tok = a.draft_tok;
+  const int32_t* __restrict__ req_offsets = a.req_offsets;
+  float* __restrict__ drafted_logit = a.drafted_logit;
+  const int B = a.B, N = a.N, H = a.H, V = a.V, w_packed = a.w_packed;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wv = wave % WV, wr = wave / WV;
-  // clear the per-request completion counters of the finishing kernel that follows
-  for (int i = blockIdx.x * T + tid; i < n_cnt; i += gridDim.x * T) done_cnt[i] = 0;
-  // consecutive tiles share W slabs and X row tiles through one XCD's L2; this launch covers
-  // slabs slab0 .. slab0 + gridDim.x / RT - 1 of the S slabs
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  int slab, rt;
-  tile_coords(tile, gridDim.x / RT, RT, blk_slabs, blk_rows, slab, rt);
-  slab += slab0;
-  const int v0 = slab * TV, r0 = rt * TR;
-  const int v_end = min(v0 + TV, V);
   const int r_last = min(r0 + TR, N) - 1;
 
   // ---- prefetch what the drafted-logit gather needs: the request offsets (to find the end
@@ -714,41 +715,32 @@ void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict
 
   // ---- the tile's logits
   typename MF::Acc acc[C::MV][C::MR];
-  if constexpr (LOOP == 1) {
-    static_assert(NST == 1, "one-slot ring");
-    lmhead_tile_1slot<TV, TR, WV, WR, BK, STREAM_W, MF>(X, W, N, H, V, v0, r0, smem, w_packed,
-                                                        acc);
-  } else if constexpr (LOOP == 2) {
+  if constexpr (F::LOOP == 2) {
     static_assert(BK == 64 && NST == 2, "two-slot spread loop: 64-deep stages");
-    lmhead_tile_spread<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, r0, smem, w_packed,
-                                                     acc);
-  } else if constexpr (LOOP == 3) {
+    lmhead_tile_spread<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
+                                                     w_packed, acc);
+  } else if constexpr (F::LOOP == 3) {
     static_assert(BK == 64 && NST == 3, "three-slot spread loop: 64-deep stages");
-    lmhead_tile_spread3<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, r0, smem, w_packed,
-                                                      acc);
+    lmhead_tile_spread3<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
+                                                      w_packed, acc);
   } else {
-    static_assert(LOOP == 0, "K loop");
-    lmhead_tile<TV, TR, WV, WR, BK, NST, STREAM_W, MF>(X, W, N, H, V, v0, r0, smem,
+    static_assert(F::LOOP == 0, "K loop");
+    lmhead_tile<TV, TR, WV, WR, BK, NST, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
                                                        w_packed, acc);
   }
 
   // Output block (i, j), register e of a lane holds vocab row kBlock i + MF::row_of(lane, e)
   // (of the wave's vocab range) and tree row kBlock j + lane % kBlock (of the wave's rows).
 
-  // Epilogue scratch reuses the ring: the gather list (kCap entries of 16 bytes), one
-  // 64 x 16-float extraction area per wave, the row-reduction exchange and two counters.
-  constexpr int kCap = 1024;
-  constexpr int kScrOff = kCap * 16;
-  constexpr int kRedOff = kScrOff + C::kWaves * kWave * 16 * 4;
-  constexpr int kCntOff = kRedOff + 3 * WV * TR * 4;
-  static_assert(kCntOff + 8 <= C::kLds, "epilogue scratch exceeds the LDS ring");
+  constexpr int kCap = C::kCap;
   char* const lds_bytes = reinterpret_cast<char*>(smem);
   int4* const s_list = reinterpret_cast<int4*>(lds_bytes);
-  float* const wscr = reinterpret_cast<float*>(lds_bytes + kScrOff) + wave * (kWave * 16);
-  float* const red_m = reinterpret_cast<float*>(lds_bytes + kRedOff);
+  float* const wscr =
+      reinterpret_cast<float*>(lds_bytes + C::kScrOff) + wave * (kWave * kRegs);
+  float* const red_m = reinterpret_cast<float*>(lds_bytes + C::kRedOff);
   float* const red_s = red_m + WV * TR;
   int* const red_a = reinterpret_cast<int*>(red_s + WV * TR);
-  int* const s_seg_end = reinterpret_cast<int*>(lds_bytes + kCntOff);
+  int* const s_seg_end = reinterpret_cast<int*>(lds_bytes + C::kCntOff);
   int* const s_cnt = s_seg_end + 1;
 
   // ---- drafted logits: nodes whose parent row and drafted token fall inside this tile.
@@ -823,14 +815,14 @@ void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict
   // Within a lane the entries of a tree row are visited in increasing vocabulary order, so
   // "strictly greater" keeps the lowest argmax; the argmax is tracked as the entry ordinal
   // k = kRegs i + e and turned into a vocabulary id afterwards, and merges keep the lowest id
-  // among equal maxima. Only the last slab needs the v < V mask. One row block at a time keeps
+  // among equal maxima. Only a wave whose ids reach past v_end needs the mask. One row block at a time keeps
   // the accumulator reads short-lived (sched_barrier stops the scheduler from hoisting them).
-  const bool full_slab = v0 + TV <= V;
   const int vwave = v0 + wv * C::kWaveV;
+  const bool full = vwave + C::kWaveV <= v_end;
   auto entry_v = [&](int k) {
     return vwave + kBlock * (k / kRegs) + MF::row_of(lane, k % kRegs);
   };
-  // Branch-free lane-local record of row block j; MASK drops entries past V (last slab).
+  // Branch-free lane-local record of row block j; MASK drops entries past v_end.
   auto row_record = [&](int j, auto mask_tag) -> Rec {
     constexpr bool MASK = decltype(mask_tag)::value;
     float m = kNegInf;
@@ -841,7 +833,7 @@ void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict
       for (int e = 0; e < kRegs; ++e) {
         const int k = kRegs * i + e;
         float z = acc[i][j][e];
-        if constexpr (MASK) z = entry_v(k) < V ? z : kNegInf;
+        if constexpr (MASK) z = entry_v(k) < v_end ? z : kNegInf;
         kbest = z > m ? k : kbest;
         m = fmaxf(m, z);
       }
@@ -852,14 +844,14 @@ void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict
 #pragma unroll
       for (int e = 0; e < kRegs; ++e) {
         const float t = exp2_rel(fmaf(acc[i][j][e], kLog2e, -mb));
-        if constexpr (MASK) sum += entry_v(kRegs * i + e) < V ? t : 0.f;
+        if constexpr (MASK) sum += entry_v(kRegs * i + e) < v_end ? t : 0.f;
         else sum += t;
       }
     return Rec{m, m == kNegInf ? 0.f : sum, m == kNegInf ? kNoIndex : entry_v(kbest)};
   };
 #pragma unroll
   for (int j = 0; j < C::MR; ++j) {
-    Rec r = full_slab ? row_record(j, std::false_type{}) : row_record(j, std::true_type{});
+    Rec r = full ? row_record(j, std::false_type{}) : row_record(j, std::true_type{});
 #pragma unroll
     for (int mask = kBlock; mask < kWave; mask <<= 1) r = rec_merge(r, rec_shfl_xor(r, mask));
     if (lane < kBlock) {
@@ -878,12 +870,43 @@ void k_lmhead_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict
                                                     red_a[w * TR + row]});
     const int n = r0 + row;
     if (n < N) {
-      const size_t at = (size_t)n * S + slab;
-      rec_m[at] = r.m;
-      rec_s[at] = r.s;
-      rec_a[at] = r.a;
+      const size_t at = (size_t)n * a.S + rec;
+      a.rec_m[at] = r.m;
+      a.rec_s[at] = r.s;
+      a.rec_a[at] = r.a;
     }
   }
+}
+
+// A launch of K1: the tiles of cut's slabs x RT row tiles (RT = 1 when the cut has a tail), on
+// family M; the tail's on family T. XCD-aware order: consecutive tiles share W slabs and X
+// row tiles through one XCD's L2 (the tail's tiles are dealt to the XCDs on their own, so that
+// every XCD gets its part of them).
+template <class M, class T>
+__global__ __launch_bounds__(M::C::kThreads, 1)
+void k_lmhead_partial(LmheadArgs a, SlabCut cut, int RT, int blk_slabs, int blk_rows) {
+  static_assert(M::C::kThreads == T::C::kThreads, "one workgroup size");
+  __shared__ uint4 smem[(M::C::kLds > T::C::kLds ? M::C::kLds : T::C::kLds) / 16];
+  // clear the per-request completion counters of the finishing kernel that follows
+  for (int i = blockIdx.x * M::C::kThreads + threadIdx.x; i < a.n_cnt;
+       i += gridDim.x * M::C::kThreads)
+    a.done_cnt[i] = 0;
+  const int main_tiles = cut.n_main * RT, bid = blockIdx.x;
+  const bool tail = bid >= main_tiles;
+  int slab, rt = 0;
+  if (tail)
+    slab = cut.n_main + xcd_tile(bid - main_tiles, gridDim.x - main_tiles);
+  else
+    tile_coords(xcd_tile(bid, main_tiles), cut.n_main, RT, blk_slabs, blk_rows, slab, rt);
+  const int width = tail ? cut.tail_width : cut.width;
+  const int v0 = cut.v_first +
+                 (tail ? cut.n_main * cut.width + (slab - cut.n_main) * width : slab * width);
+  const int v_end = min(v0 + width, a.V), r0 = rt * M::TR, rec = cut.slab0 + slab;
+  if constexpr (!std::is_same_v<M, T>) {
+    static_assert(M::TR == T::TR, "one row tile height");
+    if (tail) return lmhead_block<T>(a, v0, v_end, r0, rec, smem);
+  }
+  lmhead_block<M>(a, v0, v_end, r0, rec, smem);
 }
 
 // ---- packed weights

@@ -692,3 +692,42 @@ def test_empty_batch(asv, dev):
     o = asv.verify(**e)
     torch.cuda.synchronize()
     assert o.accepted_len.numel() == 0
+
+
+# Vocabularies on either side of every line of the cut that K1 makes up to 64 rows (on 256 CUs):
+# the narrowest slabs, one and two workgroups per CU at 128 and 224-256 ids, whole rounds with a
+# tail of 64-id slabs, of wider ones and of one id, and uncut 256-id slabs.
+@pytest.mark.parametrize("V", [5, 8191, 8193, 32768, 32769, 57344, 57345, 65537, 131072, 131073,
+                               163841, 196608, 196609, 262144, 262145])
+@pytest.mark.parametrize("sizes", [(1,), (30, 21, 13)])
+def test_rows64_vocabulary_cut(asv, dev, V, sizes):
+    """Up to 64 rows the vocabulary is cut into slabs by its size and the CU count. Against the
+    general path (the 128-row tile forced: 256-id slabs), on both weight layouts: the logits and
+    all that is decided from them bit for bit, row_lse up to the order its slab sums are added
+    in (as in test_every_tile_same_results)."""
+    import torch
+    print(f"[cut] V={V} sizes={sizes}", flush=True)
+    H, N, B = 128, sum(sizes), len(sizes)
+    g = torch.Generator(device=dev)
+    g.manual_seed(V + N)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    w = torch.empty((V, H), **bf).normal_(0, 0.1, generator=g)
+    w[V - 1] = w[0]                                   # an exact tie of the first and the last id
+    hidden = torch.empty((N, H), **bf).normal_(0, 1, generator=g)
+    off = np.cumsum((0,) + sizes).astype(np.int32)
+    parent = np.concatenate([np.r_[-1, lo + np.arange(n - 1) // 2]
+                             for lo, n in zip(off, sizes)]).astype(np.int32)
+    tok = torch.randint(0, V, (N,), dtype=torch.int32, device=dev, generator=g)
+    args = (tok, torch.from_numpy(parent).to(dev), torch.from_numpy(off).to(dev),
+            torch.full((B,), 0.2, device=dev))
+    base = asv.verify(hidden, w, *args, k1_tile=128)
+    nonroot = torch.from_numpy(parent >= 0).to(dev)
+    ws = asv.alloc_workspace(B, N, H, V, dev)
+    for weight in (w, asv.pack_lm_head(w)):
+        ws.fill_(0x7f)                                # records left unwritten would be seen
+        got = asv.verify(hidden, weight, *args, workspace=ws)
+        for f in ("row_max", "row_argmax", "accept", "accepted_len", "accepted_path",
+                  "bonus_token", "req_status"):
+            assert torch.equal(getattr(got, f), getattr(base, f)), f
+        assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
+        assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
