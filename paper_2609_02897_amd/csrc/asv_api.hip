@@ -159,6 +159,12 @@ enum class Stream64 {
   kWide256,    // <= 256 ids, two slots, two workgroups per CU
 };
 
+// <ids, rows, waves along ids, waves along rows, ring depth, K loop, non-temporal W copies>
+using Deep128 = TileFamily<128, 64, 4, 1, 3, 0, true>;
+using Deep64 = TileFamily<64, 64, 4, 1, 4, 0, true>;
+using Spread256 = TileFamily<256, 64, 2, 2, 3, 3, true>;
+using Wide256 = TileFamily<256, 64, 4, 1, 2, 0, true>;
+
 struct Cut64 {
   Stream64 kind;
   SlabCut cut;
@@ -363,8 +369,6 @@ void launch_slabs(const LmheadArgs& g, const asv_k1_launch& k, hipStream_t s,
 // Up to 64 rows: one launch over the slabs of cut_rows64.
 void launch_rows64(const LmheadArgs& g, const Cut64& c, const asv_k1_launch& k, hipStream_t s,
                    const K1Events& ev) {
-  using Deep128 = TileFamily<128, 64, 4, 1, 3, 0, true>;
-  using Deep64 = TileFamily<64, 64, 4, 1, 4, 0, true>;
   const int n_tail = c.S - c.cut.n_main;
   switch (c.kind) {
     case Stream64::kDeep128:
@@ -374,10 +378,10 @@ void launch_rows64(const LmheadArgs& g, const Cut64& c, const asv_k1_launch& k, 
         launch_lmhead<Deep128>(g, c.cut, n_tail, k, s, ev);
       break;
     case Stream64::kSpread256:
-      launch_lmhead<TileFamily<256, 64, 2, 2, 3, 3, true>>(g, c.cut, n_tail, k, s, ev);
+      launch_lmhead<Spread256>(g, c.cut, n_tail, k, s, ev);
       break;
     case Stream64::kWide256:
-      launch_lmhead<TileFamily<256, 64, 4, 1, 2, 0, true>>(g, c.cut, n_tail, k, s, ev);
+      launch_lmhead<Wide256>(g, c.cut, n_tail, k, s, ev);
       break;
   }
 }
@@ -441,30 +445,59 @@ AcceptArgs accept_args(const asv_verify_args* a, const Layout& L, char* ws, bool
 
 // ---- draft side
 
-// Tile families of the draft LM head (K5), by draft rows R = 4B. The draft vocabulary is small
-// (tens of thousands of rows), so narrow vocabulary slabs keep the launch above the CU count.
-// Beyond 64 rows the 128-row tile repeats over row tiles (a 256-row tile with the top-4
-// epilogue exceeds the register file).
-enum class DraftTile { kRows32, kRows64, kRows128 };
+// The draft LM head (K5) by draft rows R = 4B. Up to 64 rows it streams its weight like K1 and
+// runs K1's cut and tiles (cut_rows64). Beyond, one workgroup per CU: an equal share of the ids
+// where that fits a tile of 128, 192 or 256 ids (128 rows) or 128 ids (256 rows), else the rounds
+// of the cheapest of these tiles.
+enum class DraftTile { kRows64, kRows128x128, kRows128x192, kRows128x256, kRows256x128 };
 
-DraftTile pick_draft_tile(int R) {
-  if (R <= 32) return DraftTile::kRows32;
-  if (R <= 64) return DraftTile::kRows64;
-  return DraftTile::kRows128;
+struct DraftPlan {
+  DraftTile tile;
+  Cut64 cut;       // kRows64: all of it; else cut.cut and cut.S
+  int row_tiles;
+};
+
+DraftPlan plan_draft(int R, int V, int cus) {
+  if (R <= 64) return DraftPlan{DraftTile::kRows64, cut_rows64(V, cus), 1};
+  struct Family { DraftTile tile; int ids, rows, cost; };
+  // cost of one round of tiles, in us at H = 4096 (MI355X)
+  const Family families[4] = {{DraftTile::kRows128x128, 128, 128, 46},
+                              {DraftTile::kRows128x192, 192, 128, 59},
+                              {DraftTile::kRows128x256, 256, 128, 79},
+                              {DraftTile::kRows256x128, 128, 256, 59}};
+  DraftPlan best{};
+  int64_t best_est = INT64_MAX;
+  for (const Family& f : families) {
+    const int RT = (R + f.rows - 1) / f.rows;
+    const int64_t tiles = ((int64_t)V + f.ids - 1) / f.ids * RT, rounds = (tiles + cus - 1) / cus;
+    const int64_t est = rounds * f.cost;
+    if (est >= best_est) continue;
+    best_est = est;
+    // the slabs one round's row tiles leave room for, ids shared equally
+    const int64_t slabs = std::max<int64_t>(1, rounds * cus / RT);
+    const int width = (int)std::min<int64_t>(
+        f.ids, std::max<int64_t>(128, ((V + slabs - 1) / slabs + 7) / 8 * 8));
+    const int S = (V + width - 1) / width;
+    best = DraftPlan{f.tile, Cut64{Stream64::kDeep128, SlabCut{S, width, width, 0, 0}, S, false},
+                     RT};
+  }
+  return best;
 }
 
-int draft_slab(DraftTile t) { return t == DraftTile::kRows128 ? 128 : 64; }
-
 struct DraftLayout {
-  int S = 0;  // vocabulary slabs of the chosen tile
   size_t off_k = 0, off_s = 0, bytes = 0;
 };
+
+// Most records per draft row, whatever the device's CU count.
+int max_draft_records(int R, int V) {
+  const int width = R > 64 ? 128 : V <= kMaxCutVocab ? kMinCut : kSlab;
+  return (V + width - 1) / width;
+}
 
 DraftLayout draft_layout(int B, int V) {
   DraftLayout L;
   const int R = B * kTopK;
-  L.S = (V + draft_slab(pick_draft_tile(R)) - 1) / draft_slab(pick_draft_tile(R));
-  const size_t rec = (size_t)R * L.S;
+  const size_t rec = (size_t)R * max_draft_records(R, V);
   size_t at = 0;
   L.off_k = at; at += align_up(rec * kTopK * 8);
   L.off_s = at; at += align_up(rec * 4);
@@ -479,22 +512,28 @@ bool draft_sizes_ok(int B, int H, int V) {
   if ((int64_t)B * kTopK * H * 2 >= (int64_t)1 << 31) return false;
   // the draft LM head's workgroup count stays an int
   const int R = B * kTopK;
-  const DraftTile t = pick_draft_tile(R);
-  const int tr = t == DraftTile::kRows32 ? 32 : t == DraftTile::kRows64 ? 64 : 128;
-  const int64_t S = ((int64_t)V + draft_slab(t) - 1) / draft_slab(t);
+  const int tv = R <= 64 ? 64 : 128, tr = R <= 32 ? 32 : R <= 64 ? 64 : 128;
+  const int64_t S = ((int64_t)V + tv - 1) / tv;
   return S * (((int64_t)R + tr - 1) / tr) < ((int64_t)1 << 31);
 }
 
-template <int TV, int TR, int WV, int WR, int BK, int NST>
-void launch_draft(const asv_draft_args* a, const DraftLayout& L, char* ws, hipStream_t s,
-                  hipEvent_t start, hipEvent_t stop) {
-  static_assert(BK == kPackDepth && TV % kPackRowsDraft == 0 && 128 % TV == 0,
-                "a stage is one or two consecutive packed draft tiles");
-  const int R = a->B * kTopK;
-  const int RT = (R + TR - 1) / TR;
-  launch_timed(k_draft_partial<TV, TR, WV, WR, BK, NST>, L.S * RT, WV * WR * kWave, s, start, stop,
-      a->hidden, a->w_draft, R, a->H, a->V, L.S, RT, reinterpret_cast<uint64_t*>(ws + L.off_k),
-      reinterpret_cast<float*>(ws + L.off_s), a->w_draft_layout == ASV_W_PACKED ? 128 : 0);
+template <class M, class T = M>
+void launch_draft(const asv_draft_args* a, const DraftLayout& L, char* ws, const DraftPlan& p,
+                  hipStream_t s, const K1Events& ev) {
+  static_assert(M::BK == kPackDepth, "a stage is one packed column block");
+  DraftArgs g;
+  g.X = a->hidden;
+  g.W = a->w_draft;
+  g.R = a->B * kTopK;
+  g.H = a->H;
+  g.V = a->V;
+  g.S = p.cut.S;
+  g.rec_k = reinterpret_cast<uint64_t*>(ws + L.off_k);
+  g.rec_s = reinterpret_cast<float*>(ws + L.off_s);
+  g.w_packed = a->w_draft_layout == ASV_W_PACKED ? 128 : 0;
+  const int n_main = p.cut.cut.n_main;
+  launch_timed(k_draft_partial<M, T>, n_main * p.row_tiles + p.cut.S - n_main, M::C::kThreads, s,
+               ev.start, ev.stop, g, p.cut.cut, p.row_tiles);
 }
 
 // ---- static scratch of asv_verify_noalloc
@@ -757,24 +796,46 @@ extern "C" int asv_draft_step_tuned(const asv_draft_args* a, const asv_tuning* t
   char* ws = static_cast<char*>(workspace);
   (void)hipGetLastError();
   // timing events (measurement only): the start and the end of the draft LM head's launch
-  const hipEvent_t ev_begin = reinterpret_cast<hipEvent_t>(tu.begin_event);
-  const hipEvent_t ev_end = reinterpret_cast<hipEvent_t>(tu.end_event);
-  switch (pick_draft_tile(a->B * kTopK)) {
-    // <vocab rows, draft rows, waves along vocab, waves along rows, K per stage, ring depth>
-    case DraftTile::kRows32:
-      launch_draft<64, 32, 2, 1, 64, 4>(a, L, ws, s, ev_begin, ev_end);
-      break;
+  const K1Events ev{reinterpret_cast<hipEvent_t>(tu.begin_event),
+                    reinterpret_cast<hipEvent_t>(tu.end_event)};
+  const DraftPlan p = plan_draft(a->B * kTopK, a->V, cu_count());
+  switch (p.tile) {
     case DraftTile::kRows64:
-      launch_draft<64, 64, 2, 2, 64, 4>(a, L, ws, s, ev_begin, ev_end);
+      switch (p.cut.kind) {
+        case Stream64::kDeep128:
+          if (p.cut.tail64)
+            launch_draft<Deep128, Deep64>(a, L, ws, p, s, ev);
+          else
+            launch_draft<Deep128>(a, L, ws, p, s, ev);
+          break;
+        case Stream64::kSpread256: launch_draft<Spread256>(a, L, ws, p, s, ev); break;
+        case Stream64::kWide256: launch_draft<Wide256>(a, L, ws, p, s, ev); break;
+      }
       break;
-    case DraftTile::kRows128:
-      launch_draft<128, 128, 2, 4, 64, 3>(a, L, ws, s, ev_begin, ev_end);
+    // <ids, draft rows, waves along ids, waves along rows, ring depth, K loop, non-temporal W
+    // copies, MFMA shape>. Eight waves: one workgroup per CU needs them to keep copies and MFMAs
+    // in flight. The spread loop on the wider tiles (128 ids x 256 rows: 59 us a round against
+    // 72 us with the burst ring); the 128x128 tile is MFMA-light and 2-5% faster on the burst
+    // ring (32000 ids, 80 and 128 rows), where the 32x32 shape's cheaper epilogue (one lane
+    // merge instead of two, on half as many row blocks) is worth another 1-3%. The hint pays on
+    // the others (64000 ids, 128 rows: 294 -> 284 us for three steps; 256 rows: 450 -> 432).
+    case DraftTile::kRows128x128:
+      launch_draft<TileFamily<128, 128, 2, 4, 3, 0, false, Mfma32>>(a, L, ws, p, s, ev);
+      break;
+    case DraftTile::kRows128x192:
+      launch_draft<TileFamily<192, 128, 2, 4, 3, 3, true>>(a, L, ws, p, s, ev);
+      break;
+    case DraftTile::kRows128x256:
+      launch_draft<TileFamily<256, 128, 2, 4, 3, 3, true>>(a, L, ws, p, s, ev);
+      break;
+    case DraftTile::kRows256x128:
+      launch_draft<TileFamily<128, 256, 2, 4, 3, 3, true>>(a, L, ws, p, s, ev);
       break;
   }
   if (int rc = launch_status("k_draft_partial")) return rc;
   DraftGrowArgs g;
   g.B = a->B;
-  g.S = L.S;
+  g.S = p.cut.S;
   g.step = a->step;
   g.rec_k = reinterpret_cast<const uint64_t*>(ws + L.off_k);
   g.rec_s = reinterpret_cast<const float*>(ws + L.off_s);

@@ -46,6 +46,36 @@ __device__ __forceinline__ Rec rec_shfl_xor(Rec x, int mask) {
   return y;
 }
 
+// The values of x in the two 16-lane rows of each half wave (STEP = 16: rows 0 and 1, or 2 and 3),
+// or in the two half waves (STEP = 32), by v_permlane16_swap / v_permlane32_swap: `first` is the
+// lower one's, `second` the upper one's, the same in both, so a merge (first, second) leaves its
+// result on either side. Two moves and the swap, in place of a round trip through the LDS
+// permute unit.
+template <int STEP>
+__device__ __forceinline__ void lane_halves(uint32_t x, uint32_t& first, uint32_t& second) {
+  static_assert(STEP == 16 || STEP == 32, "rows or half waves");
+  if constexpr (STEP == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    first = r[0];
+    second = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    first = r[0];
+    second = r[1];
+  }
+}
+
+// The merge of the records that the lanes l, l ^ STEP hold, lower lane first; both get it.
+template <int STEP>
+__device__ __forceinline__ Rec rec_merge_lanes(Rec x) {
+  uint32_t m[2], s[2], a[2];
+  lane_halves<STEP>(__float_as_uint(x.m), m[0], m[1]);
+  lane_halves<STEP>(__float_as_uint(x.s), s[0], s[1]);
+  lane_halves<STEP>((uint32_t)x.a, a[0], a[1]);
+  return rec_merge(Rec{__uint_as_float(m[0]), __uint_as_float(s[0]), (int)a[0]},
+                   Rec{__uint_as_float(m[1]), __uint_as_float(s[1]), (int)a[1]});
+}
+
 // Full-wave reduction; every lane ends with the merged record.
 __device__ __forceinline__ Rec rec_wave_reduce(Rec x) {
 #pragma unroll

@@ -2,7 +2,7 @@
 // and log-sum-exp, one growth step of every request's draft tree, and the final pruning to the
 // verification budget.
 //
-// K5 k_draft_partial: the LM-head tile of K1 (same staging, MFMA and accumulator layout) with a
+// K5 k_draft_partial: the LM-head tiles of K1 (same staging, MFMA and accumulator layout) with a
 //   top-4 epilogue: per (draft row, vocabulary slab) it writes the slab's four best (logit, id)
 //   pairs, best first, as 64-bit order keys, and the sum of exp(z - best). The logits never
 //   reach memory.
@@ -101,19 +101,25 @@ __device__ __forceinline__ Top4 top4_merge(const Top4& a, const Top4& b) {
   return c;
 }
 
-__device__ __forceinline__ uint64_t shfl_xor64(uint64_t x, int mask) {
-  const uint32_t lo = __shfl_xor((uint32_t)x, mask, kWave);
-  const uint32_t hi = __shfl_xor((uint32_t)(x >> 32), mask, kWave);
-  return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ Top4 top4_shfl_xor(const Top4& x, int mask) {
-  Top4 y;
+// The merge of the records that the lanes l, l ^ STEP hold (rec_merge_lanes); both get it.
+template <int STEP>
+__device__ __forceinline__ Top4 top4_merge_lanes(const Top4& x) {
+  Top4 t[2];
+  uint32_t w[2];
 #pragma unroll
-  for (int q = 0; q < kTopK; ++q) y.k[q] = shfl_xor64(x.k[q], mask);
-  y.m = __shfl_xor(x.m, mask, kWave);
-  y.s = __shfl_xor(x.s, mask, kWave);
-  return y;
+  for (int q = 0; q < kTopK; ++q) {
+    uint32_t hi[2];
+    lane_halves<STEP>((uint32_t)x.k[q], w[0], w[1]);
+    lane_halves<STEP>((uint32_t)(x.k[q] >> 32), hi[0], hi[1]);
+    t[0].k[q] = ((uint64_t)hi[0] << 32) | w[0];
+    t[1].k[q] = ((uint64_t)hi[1] << 32) | w[1];
+  }
+  t[0].m = key_value(t[0].k[0]);
+  t[1].m = key_value(t[1].k[0]);
+  lane_halves<STEP>(__float_as_uint(x.s), w[0], w[1]);
+  t[0].s = __uint_as_float(w[0]);
+  t[1].s = __uint_as_float(w[1]);
+  return top4_merge(t[0], t[1]);
 }
 
 template <int N>
@@ -160,44 +166,50 @@ __device__ __forceinline__ Top4 top4_wave_reduce(Top4 t) {
 
 // ------------------------------------------------------------------------------------------ K5
 
-template <int TV, int TR, int WV, int WR, int BK, int NST>
-__global__ __launch_bounds__(WV * WR * kWave, 1)
-void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int R,
-                     int H, int V, int S, int RT, uint64_t* __restrict__ rec_k,
-                     float* __restrict__ rec_s, int w_packed) {
-  using C = LmheadCfg<TV, TR, WV, WR, BK, NST>;
-  constexpr int T = C::kThreads;
-  __shared__ uint4 smem[C::kLds / 16];
+struct DraftArgs {
+  const uint16_t* X;
+  const uint16_t* W;
+  int R, H, V;
+  int S;                         // records per draft row
+  uint64_t* rec_k;
+  float* rec_s;
+  int w_packed;                  // 0: W row-major; else packed, V rounded up to this many rows
+};
 
+// One tile: ids v0 .. v_end - 1, draft rows r0 .. r0 + TR - 1; `rec` is the record of its rows.
+template <class F>
+__device__ __forceinline__ void draft_block(const DraftArgs& a, int v0, int v_end, int r0, int rec,
+                                            uint4* smem) {
+  using C = typename F::C;
+  using MF = typename F::MF;
+  constexpr int TR = F::TR, WV = F::WV, T = C::kThreads;
+  constexpr int kBlock = MF::kBlock, kRegs = MF::kRegs, kEntries = C::MV * kRegs;
+  const int R = a.R;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wv = wave % WV, wr = wave / WV;
-  const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int slab = tile / RT, rt = tile % RT;
-  const int v0 = slab * TV, r0 = rt * TR;
 
-  f32x16 acc[C::MV][C::MR];
-  // The non-temporal hint on the W copies pays for tiles of up to 64 rows (4 rows: 5% less
-  // time after a cache flush); the 128-row tile is faster without it, because the draft
-  // weight (262 MB at 32000 ids) largely fits the last-level cache.
-  lmhead_tile<TV, TR, WV, WR, BK, NST, (TR <= 64)>(X, W, R, H, V, v0, min(v0 + TV, V), r0,
-                                                  smem, w_packed, acc);
+  typename MF::Acc acc[C::MV][C::MR];
+  family_tile<F>(a.X, a.W, R, a.H, a.V, v0, v_end, r0, smem, a.w_packed, acc);
 
-  // Output block (i, j), register e of a lane holds vocabulary row
-  //   v0 + wv * kWaveV + 32 i + 8 (e / 4) + 4 (lane / 32) + e % 4   and
-  // tree row wr * kWaveR + 32 j + lane % 32. For a fixed lane the entry ordinal k = 16 i + e
-  // visits the lane's vocabulary ids in increasing order.
-  const bool full_slab = v0 + TV <= V;
-  const int vlane = v0 + wv * C::kWaveV + 4 * (lane >> 5);
-  auto entry_v = [&](int k) { return vlane + 32 * (k >> 4) + 8 * ((k & 15) >> 2) + (k & 3); };
+  // Output block (i, j), register e of a lane holds vocabulary row kBlock i + MF::row_of(lane, e)
+  // (of the wave's vocabulary range) and draft row kBlock j + lane % kBlock (of the wave's rows).
+  // For a fixed lane the entry ordinal k = kRegs i + e visits its ids in increasing order.
+  const int vwave = v0 + wv * C::kWaveV;
+  const bool full = vwave + C::kWaveV <= v_end;
+  auto entry_v = [&](int k) {
+    return vwave + kBlock * (k / kRegs) + MF::row_of(lane, k % kRegs);
+  };
   // Lane-local top-4 of row block j: the first four entries sorted, then every later entry
   // inserted where it beats a kept one strictly (it has the highest id so far, so it loses
-  // ties). MASK drops entries past V (last slab).
+  // ties). MASK takes entries past v_end as -inf; none of them reaches a row's top 4, since the
+  // first slab's ids 0 .. 3 come before them at equal logits.
+  static_assert(kEntries >= kTopK, "a lane holds at least four entries");
   auto lane_top4 = [&](int j, auto mask_tag) -> Top4 {
     constexpr bool MASK = decltype(mask_tag)::value;
     auto entry = [&](int k) {
-      float z = fmaxf(acc[k >> 4][j][k & 15], kNegInf);    // a non-number becomes -inf
-      if constexpr (MASK) z = entry_v(k) < V ? z : kNegInf;
+      float z = fmaxf(acc[k / kRegs][j][k % kRegs], kNegInf);    // a non-number becomes -inf
+      if constexpr (MASK) z = entry_v(k) < v_end ? z : kNegInf;
       return z;
     };
     float v[kTopK];
@@ -213,7 +225,7 @@ void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict_
     pair_order(v[1], id[1], v[3], id[3]);
     pair_order(v[1], id[1], v[2], id[2]);
 #pragma unroll
-    for (int k = kTopK; k < C::MV * 16; ++k) {
+    for (int k = kTopK; k < kEntries; ++k) {
       const float z = entry(k);
       const int e = entry_v(k);
       const bool b0 = z > v[0], b1 = z > v[1], b2 = z > v[2], b3 = z > v[3];
@@ -229,7 +241,7 @@ void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict_
     const float mb = v[0] * kLog2e;
     float sum = 0.f;
 #pragma unroll
-    for (int k = 0; k < C::MV * 16; ++k) sum += exp2_rel(fmaf(entry(k), kLog2e, -mb));
+    for (int k = 0; k < kEntries; ++k) sum += exp2_rel(fmaf(entry(k), kLog2e, -mb));
     Top4 t;
 #pragma unroll
     for (int k = 0; k < kTopK; ++k) t.k[k] = pair_key(v[k], id[k]);
@@ -245,11 +257,12 @@ void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict_
   static_assert(WV * TR * (8 * kTopK + 4) <= C::kLds, "exchange area exceeds the ring");
 #pragma unroll
   for (int j = 0; j < C::MR; ++j) {
-    if (r0 + wr * C::kWaveR + 32 * j >= R) continue;        // row block past the last row
-    Top4 t = full_slab ? lane_top4(j, std::false_type{}) : lane_top4(j, std::true_type{});
-    t = top4_merge(t, top4_shfl_xor(t, 32));
-    if (lane < 32) {
-      const int at = wv * TR + wr * C::kWaveR + 32 * j + lane;
+    if (r0 + wr * C::kWaveR + kBlock * j >= R) continue;    // row block past the last row
+    Top4 t = full ? lane_top4(j, std::false_type{}) : lane_top4(j, std::true_type{});
+    if constexpr (kBlock == 16) t = top4_merge_lanes<16>(t);   // lane groups of a draft row
+    t = top4_merge_lanes<32>(t);
+    if (lane < kBlock) {
+      const int at = wv * TR + wr * C::kWaveR + kBlock * j + lane;
 #pragma unroll
       for (int k = 0; k < kTopK; ++k) x_k[at * kTopK + k] = t.k[k];
       x_s[at] = t.s;
@@ -272,14 +285,27 @@ void k_draft_partial(const uint16_t* __restrict__ X, const uint16_t* __restrict_
     Top4 t = load(0);
 #pragma unroll
     for (int w = 1; w < WV; ++w) t = top4_merge(t, load(w));
-    const size_t at = (size_t)n * S + slab;
-    uint4* const dst = reinterpret_cast<uint4*>(rec_k + at * kTopK);
+    const size_t at = (size_t)n * a.S + rec;
+    uint4* const dst = reinterpret_cast<uint4*>(a.rec_k + at * kTopK);
     dst[0] = make_uint4((uint32_t)t.k[0], (uint32_t)(t.k[0] >> 32), (uint32_t)t.k[1],
                         (uint32_t)(t.k[1] >> 32));
     dst[1] = make_uint4((uint32_t)t.k[2], (uint32_t)(t.k[2] >> 32), (uint32_t)t.k[3],
                         (uint32_t)(t.k[3] >> 32));
-    rec_s[at] = t.s;
+    a.rec_s[at] = t.s;
   }
+}
+
+// A launch of K5: the tiles of cut's slabs x RT row tiles on family M, the tail's on family T.
+template <class M, class T>
+__global__ __launch_bounds__(M::C::kThreads, 1)
+void k_draft_partial(DraftArgs a, SlabCut cut, int RT) {
+  static_assert(M::C::kThreads == T::C::kThreads && M::TR == T::TR, "one workgroup shape");
+  __shared__ uint4 smem[(M::C::kLds > T::C::kLds ? M::C::kLds : T::C::kLds) / 16];
+  const TileAt t = tile_at(cut, a.V, RT, 0, 0);
+  if constexpr (!std::is_same_v<M, T>) {
+    if (t.tail) return draft_block<T>(a, t.v0, t.v_end, 0, t.rec, smem);
+  }
+  draft_block<M>(a, t.v0, t.v_end, t.rt * M::TR, t.rec, smem);
 }
 
 // ------------------------------------------------------------------------------------------ K6

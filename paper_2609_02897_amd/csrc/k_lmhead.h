@@ -18,10 +18,10 @@
 // ds_read_b128 in the MFMA operand layout is free of bank conflicts. K1 runs
 // v_mfma_f32_16x16x32_bf16 with A = W (16 vocabulary rows) and B = X (16 tree rows): each lane
 // then owns one tree row and 4 vocabulary entries of every 16x16 output block, so the per-row
-// reduction is mostly lane-local, with two cross-lane steps. (The draft LM head, which shares
-// the burst ring, runs v_mfma_f32_32x32x16_bf16: 16 entries of a 32x32 block per lane.) In
-// every comparison made the two shapes gave bit-identical logits; the 16x16x32 form lets the
-// chip hold a higher clock under K1's sustained MFMA load. Fragments of a later K step are read while the current MFMAs run.
+// reduction is mostly lane-local, with two cross-lane steps. The draft LM head runs the same
+// tiles with an epilogue of its own (one of them on v_mfma_f32_32x32x16_bf16: 16 entries of a
+// 32x32 block per lane; the two shapes give the same logits bit for bit). Fragments of a later K step are read while the current MFMAs
+// run.
 // Every loop accumulates K in increasing order, so all tiles give the same logits bit for bit.
 #pragma once
 
@@ -152,7 +152,7 @@ __device__ __forceinline__ void wait_stage_barrier(int newer) {
   else wait_vm_barrier<0>();
 }
 
-template <int TV, int TR, int WV, int WR, int BK, int NST, class MF = Mfma32>
+template <int TV, int TR, int WV, int WR, int BK, int NST, class MF = Mfma16>
 struct LmheadCfg {
   static constexpr int kWaves = WV * WR;
   static constexpr int kThreads = kWaves * kWave;
@@ -246,7 +246,7 @@ __host__ __device__ __forceinline__ void tile_coords(int t, int n_slabs, int RT,
 // for more row tiles, which share each W slab through an XCD's L2 (with the hint: 378 rows'
 // three 128-row tiles a slab about 2% slower, 2048 and 3048 rows 1.5% and 4.5%).
 template <int TV, int TR, int WV, int WR, int BK, int NST, bool STREAM_W = (TR <= 128),
-          class MF = Mfma32>
+          class MF = Mfma16>
 struct TileIo {
   using C = LmheadCfg<TV, TR, WV, WR, BK, NST, MF>;
   static constexpr int CPR = C::CPR;
@@ -358,7 +358,7 @@ __device__ __forceinline__ void zero_acc(Acc (&acc)[MV][MR]) {
 // stage copy has landed and the workgroup has passed a barrier, so the caller may reuse the
 // LDS ring.
 template <int TV, int TR, int WV, int WR, int BK, int NST, bool STREAM_W = (TR <= 128),
-          class MF = Mfma32>
+          class MF = Mfma16>
 __device__ __forceinline__ void lmhead_tile(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
     int v0, int v_end, int r0, uint4* smem, int w_packed,
@@ -446,7 +446,7 @@ __device__ __forceinline__ void wait_lds_barrier() {
 // accumulate in the same K order as lmhead_tile, so the logits are bit-identical. The
 // schedule is branch-free: past the last stage the copies repeat the last stage into the slot
 // just freed (never read again) and the reads of the stage after the last are discarded.
-template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma32>
+template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma16>
 __device__ __forceinline__ void lmhead_tile_spread(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
     int v0, int v_end, int r0, uint4* smem, int w_packed,
@@ -549,7 +549,7 @@ __device__ __forceinline__ void lmhead_tile_spread(
 //   m >= Q2         read the first half's fragments of stage k + 1; the first copies of
 //                   stage k + 3.
 // Past the last stage the copies repeat the last stage into slots no later stage reads.
-template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma32>
+template <int TV, int TR, int WV, int WR, bool STREAM_W, class MF = Mfma16>
 __device__ __forceinline__ void lmhead_tile_spread3(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V,
     int v0, int v_end, int r0, uint4* smem, int w_packed,
@@ -660,22 +660,70 @@ struct SlabCut {
 // cache policy (see TileIo); it changes no result. MF is the MFMA shape; every tile family of K1
 // runs the same one, so that all of them sum each logit's products in the same order and give
 // the same logits bit for bit.
-template <int TV_, int TR_, int WV_, int WR_, int NST_, int LOOP_, bool STREAM_W_>
+template <int TV_, int TR_, int WV_, int WR_, int NST_, int LOOP_, bool STREAM_W_,
+          class MF_ = Mfma16>
 struct TileFamily {
   static constexpr int TV = TV_, TR = TR_, WV = WV_, WR = WR_, BK = 64, NST = NST_, LOOP = LOOP_;
   static constexpr bool STREAM_W = STREAM_W_;
-  using MF = Mfma16;
+  using MF = MF_;
   using C = LmheadCfg<TV, TR, WV, WR, BK, NST, MF>;
   static_assert(C::kCntOff + 8 <= C::kLds, "epilogue scratch exceeds the LDS ring");
 };
+
+// The logits of one tile of family F (see lmhead_tile), by its K loop.
+template <class F>
+__device__ __forceinline__ void family_tile(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, int N, int H, int V, int v0,
+    int v_end, int r0, uint4* smem, int w_packed,
+    typename F::MF::Acc (&acc)[F::C::MV][F::C::MR]) {
+  using MF = typename F::MF;
+  if constexpr (F::LOOP == 2) {
+    static_assert(F::NST == 2, "two-slot spread loop");
+    lmhead_tile_spread<F::TV, F::TR, F::WV, F::WR, F::STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0,
+                                                                   smem, w_packed, acc);
+  } else if constexpr (F::LOOP == 3) {
+    static_assert(F::NST == 3, "three-slot spread loop");
+    lmhead_tile_spread3<F::TV, F::TR, F::WV, F::WR, F::STREAM_W, MF>(X, W, N, H, V, v0, v_end,
+                                                                    r0, smem, w_packed, acc);
+  } else {
+    static_assert(F::LOOP == 0, "K loop");
+    lmhead_tile<F::TV, F::TR, F::WV, F::WR, F::BK, F::NST, F::STREAM_W, MF>(
+        X, W, N, H, V, v0, v_end, r0, smem, w_packed, acc);
+  }
+}
+
+// The tile of workgroup blockIdx.x in a launch over cut's slabs x RT row tiles (RT = 1 when the
+// cut has a tail): consecutive tiles share W slabs and X row tiles through one XCD's L2; the
+// tail's tiles are dealt to the XCDs on their own, so that every XCD gets its part of them.
+struct TileAt {
+  int v0, v_end, rt, rec;
+  bool tail;
+};
+__device__ __forceinline__ TileAt tile_at(const SlabCut& cut, int V, int RT, int blk_slabs,
+                                          int blk_rows) {
+  const int main_tiles = cut.n_main * RT, bid = blockIdx.x;
+  TileAt t;
+  t.tail = bid >= main_tiles;
+  t.rt = 0;
+  int slab;
+  if (t.tail)
+    slab = cut.n_main + xcd_tile(bid - main_tiles, gridDim.x - main_tiles);
+  else
+    tile_coords(xcd_tile(bid, main_tiles), cut.n_main, RT, blk_slabs, blk_rows, slab, t.rt);
+  const int width = t.tail ? cut.tail_width : cut.width;
+  t.v0 = cut.v_first +
+         (t.tail ? cut.n_main * cut.width + (slab - cut.n_main) * width : slab * width);
+  t.v_end = min(t.v0 + width, V);
+  t.rec = cut.slab0 + slab;
+  return t;
+}
 
 // One tile: ids v0 .. v_end - 1 (at most TV), tree rows r0 .. r0 + TR - 1; `rec` is the record
 // each of its rows writes.
 template <class F>
 __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_end, int r0,
                                              int rec, uint4* smem) {
-  constexpr int TV = F::TV, TR = F::TR, WV = F::WV, WR = F::WR, BK = F::BK, NST = F::NST;
-  constexpr bool STREAM_W = F::STREAM_W;
+  constexpr int TR = F::TR, WV = F::WV;
   using MF = typename F::MF;
   using C = typename F::C;
   constexpr int T = C::kThreads;
@@ -715,19 +763,7 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
 
   // ---- the tile's logits
   typename MF::Acc acc[C::MV][C::MR];
-  if constexpr (F::LOOP == 2) {
-    static_assert(BK == 64 && NST == 2, "two-slot spread loop: 64-deep stages");
-    lmhead_tile_spread<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
-                                                     w_packed, acc);
-  } else if constexpr (F::LOOP == 3) {
-    static_assert(BK == 64 && NST == 3, "three-slot spread loop: 64-deep stages");
-    lmhead_tile_spread3<TV, TR, WV, WR, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
-                                                      w_packed, acc);
-  } else {
-    static_assert(F::LOOP == 0, "K loop");
-    lmhead_tile<TV, TR, WV, WR, BK, NST, STREAM_W, MF>(X, W, N, H, V, v0, v_end, r0, smem,
-                                                       w_packed, acc);
-  }
+  family_tile<F>(X, W, N, H, V, v0, v_end, r0, smem, w_packed, acc);
 
   // Output block (i, j), register e of a lane holds vocab row kBlock i + MF::row_of(lane, e)
   // (of the wave's vocab range) and tree row kBlock j + lane % kBlock (of the wave's rows).
@@ -878,35 +914,21 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
   }
 }
 
-// A launch of K1: the tiles of cut's slabs x RT row tiles (RT = 1 when the cut has a tail), on
-// family M; the tail's on family T. XCD-aware order: consecutive tiles share W slabs and X
-// row tiles through one XCD's L2 (the tail's tiles are dealt to the XCDs on their own, so that
-// every XCD gets its part of them).
+// A launch of K1: the tiles of cut's slabs x RT row tiles on family M, the tail's on family T.
 template <class M, class T>
 __global__ __launch_bounds__(M::C::kThreads, 1)
 void k_lmhead_partial(LmheadArgs a, SlabCut cut, int RT, int blk_slabs, int blk_rows) {
-  static_assert(M::C::kThreads == T::C::kThreads, "one workgroup size");
+  static_assert(M::C::kThreads == T::C::kThreads && M::TR == T::TR, "one workgroup shape");
   __shared__ uint4 smem[(M::C::kLds > T::C::kLds ? M::C::kLds : T::C::kLds) / 16];
   // clear the per-request completion counters of the finishing kernel that follows
   for (int i = blockIdx.x * M::C::kThreads + threadIdx.x; i < a.n_cnt;
        i += gridDim.x * M::C::kThreads)
     a.done_cnt[i] = 0;
-  const int main_tiles = cut.n_main * RT, bid = blockIdx.x;
-  const bool tail = bid >= main_tiles;
-  int slab, rt = 0;
-  if (tail)
-    slab = cut.n_main + xcd_tile(bid - main_tiles, gridDim.x - main_tiles);
-  else
-    tile_coords(xcd_tile(bid, main_tiles), cut.n_main, RT, blk_slabs, blk_rows, slab, rt);
-  const int width = tail ? cut.tail_width : cut.width;
-  const int v0 = cut.v_first +
-                 (tail ? cut.n_main * cut.width + (slab - cut.n_main) * width : slab * width);
-  const int v_end = min(v0 + width, a.V), r0 = rt * M::TR, rec = cut.slab0 + slab;
+  const TileAt t = tile_at(cut, a.V, RT, blk_slabs, blk_rows);
   if constexpr (!std::is_same_v<M, T>) {
-    static_assert(M::TR == T::TR, "one row tile height");
-    if (tail) return lmhead_block<T>(a, v0, v_end, r0, rec, smem);
+    if (t.tail) return lmhead_block<T>(a, t.v0, t.v_end, 0, t.rec, smem);
   }
-  lmhead_block<M>(a, v0, v_end, r0, rec, smem);
+  lmhead_block<M>(a, t.v0, t.v_end, t.rt * M::TR, t.rec, smem);
 }
 
 // ---- packed weights

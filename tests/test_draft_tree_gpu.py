@@ -647,3 +647,46 @@ def test_many_requests(asv, dev):
     assert list(c_off.cpu().numpy()) == list(ref["off"]) and not cst.cpu().numpy().any()
     assert list(c_tok.cpu().numpy()[:total]) == list(ref["tok"])
     assert list(c_row.cpu().numpy()[:total]) == list(ref["row"])
+
+
+# Sizes on either side of every line of the draft LM head's plan (on 256 CUs): up to 64 rows the
+# vocabulary's cut, beyond it one round of 128-, 192- and 256-id tiles (the row tile's remainders
+# among them), the rounds of the cheapest one, and two row tiles of 256.
+@pytest.mark.parametrize("B,V", [(1, 4), (1, 8193), (16, 32769), (9, 57345), (16, 65537), (5, 131073),
+                                 (2, 163841), (3, 262145), (17, 4), (17, 32768), (32, 32769),
+                                 (20, 49153), (32, 65537), (32, 98305), (33, 32768), (64, 32769),
+                                 (65, 5000)])
+def test_draft_plan_edges(asv, dev, B, V):
+    """Top-4, log-probabilities and row_lse against float64 for each tile and cut, both weight
+    layouts. H = 64: float32 sums of 64 products of bf16 values with |z| < 16 are within 64 * 16 *
+    2^-24 = 6e-5 of float64's, so ids are compared where the next logit is 1e-4 away."""
+    import torch
+    print(f"[draft plan] B={B} V={V}", flush=True)
+    H, R = 64, 4 * B
+    g = torch.Generator(device=dev)
+    g.manual_seed(B * 7 + V)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    w = torch.empty((V, H), **bf).normal_(0, 0.15, generator=g)
+    w[V - 1] = w[0]                                   # exact tie: the lower id comes first
+    x = torch.empty((R, H), **bf).normal_(0, 1, generator=g)
+    x[0] = w[0] * 8                                   # and it is row 0's top-1
+    z = x.double() @ w.double().T
+    lse = torch.logsumexp(z, 1)
+    best, ids = z.topk(min(5, V), dim=1)
+    outs = []
+    for weight in (w, asv.pack_draft_head(w)):
+        ws = torch.full((max(asv.draft_workspace_bytes(B, H, V), 256),), 0xff, dtype=torch.uint8,
+                        device=dev)                   # keys left unwritten would come first
+        o = asv.draft_step(x, weight, asv.alloc_draft_trees(B, dev), 0, shape=(3, 4, 4),
+                           workspace=ws)
+        outs.append(o)
+        assert (o.row_lse - lse).abs().max() < 1e-4
+        assert (o.topk_logp - (best[:, :4] - lse[:, None])).abs().max() < 1e-4
+        gap = best[:, :-1] - best[:, 1:]              # clear of both neighbours
+        clear = torch.ones((R, 4), dtype=torch.bool, device=dev)
+        clear[:, :gap.shape[1]] &= gap[:, :4] > 1e-4
+        clear[:, 1:] &= gap[:, :3] > 1e-4
+        assert torch.equal(o.topk_id[clear], ids[:, :4][clear].to(torch.int32))
+        assert o.topk_id[0, :2].tolist() == [0, V - 1]
+    for f in ("topk_id", "topk_logp", "row_lse", "front_tok"):
+        assert torch.equal(getattr(outs[0], f), getattr(outs[1], f)), f
