@@ -888,8 +888,8 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
 #pragma unroll
   for (int j = 0; j < C::MR; ++j) {
     Rec r = full ? row_record(j, std::false_type{}) : row_record(j, std::true_type{});
-#pragma unroll
-    for (int mask = kBlock; mask < kWave; mask <<= 1) r = rec_merge(r, rec_shfl_xor(r, mask));
+    static_assert(kBlock == 16, "the lane groups of a tree row are the wave's four 16-lane rows");
+    r = rec_merge_lanes<32>(rec_merge_lanes<16>(r));
     if (lane < kBlock) {
       const int row = wr * C::kWaveR + kBlock * j + lane;
       red_m[wv * TR + row] = r.m;
