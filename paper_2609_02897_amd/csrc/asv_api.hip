@@ -848,7 +848,11 @@ extern "C" int asv_draft_step_tuned(const asv_draft_args* a, const asv_tuning* t
   g.row_lse = a->row_lse;
   g.front_tok = a->front_tok;
   g.draft_conf = a->draft_conf;
-  k_draft_grow<<<a->B, kDraftThreads, 0, s>>>(g);
+  // the records of a row in one round of loads: four a lane up to 256 of them, else eight
+  if (g.S <= 4 * kWave)
+    k_draft_grow<4><<<a->B, kDraftThreads, 0, s>>>(g);
+  else
+    k_draft_grow<8><<<a->B, kDraftThreads, 0, s>>>(g);
   return launch_status("k_draft_grow");
 }
 

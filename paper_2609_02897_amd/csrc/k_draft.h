@@ -24,7 +24,6 @@ namespace asv {
 constexpr int kTopK = ASV_TOPK_MAX;   // 4
 constexpr int kPoolMax = ASV_POOL_MAX;
 constexpr int kDraftThreads = kTopK * kWave;
-constexpr int kGrowBatch = 8;         // slab records a lane loads before merging them
 
 __device__ __forceinline__ bool pair_better(float va, int ia, float vb, int ib) {
   return va > vb || (va == vb && ia < ib);
@@ -330,6 +329,8 @@ __device__ __forceinline__ bool draft_shape_ok(int nsteps, int topk, int ndt) {
          nsteps <= kPoolMax && topk + (nsteps - 1) * topk * topk <= kPoolMax;
 }
 
+// BATCH: slab records a lane loads before merging them (64 BATCH records in one round of loads).
+template <int BATCH>
 __global__ __launch_bounds__(kDraftThreads)
 void k_draft_grow(DraftGrowArgs a) {
   __shared__ int s_id[kTopK][kTopK];
@@ -381,13 +382,13 @@ void k_draft_grow(DraftGrowArgs a) {
   }
 
   // ---- merge the S slab records of this wave's row: lane l takes slabs l, l + 64, ...,
-  // kGrowBatch at a time, all loads of a batch issued before any merge (addresses clamped into
+  // BATCH at a time, all loads of a batch issued before any merge (addresses clamped into
   // the row, slots past S masked afterwards), merged as a pairwise tree
   Top4 t = top4_empty();
-  for (int base = 0; base < a.S; base += kWave * kGrowBatch) {
-    Top4 r[kGrowBatch];
+  for (int base = 0; base < a.S; base += kWave * BATCH) {
+    Top4 r[BATCH];
 #pragma unroll
-    for (int q = 0; q < kGrowBatch; ++q) {
+    for (int q = 0; q < BATCH; ++q) {
       const int sl = base + q * kWave + lane;
       const size_t at = (size_t)row * a.S + min(sl, a.S - 1);
       const uint4* const src = reinterpret_cast<const uint4*>(a.rec_k + at * kTopK);
@@ -400,16 +401,17 @@ void k_draft_grow(DraftGrowArgs a) {
       r[q].s = a.rec_s[at];
     }
 #pragma unroll
-    for (int q = 0; q < kGrowBatch; ++q)
+    for (int q = 0; q < BATCH; ++q)
       if (base + q * kWave + lane >= a.S) r[q] = top4_empty();
 #pragma unroll
-    for (int w = 1; w < kGrowBatch; w *= 2)
+    for (int w = 1; w < BATCH; w *= 2)
 #pragma unroll
-      for (int q = 0; q + w < kGrowBatch; q += 2 * w) r[q] = top4_merge(r[q], r[q + w]);
+      for (int q = 0; q + w < BATCH; q += 2 * w) r[q] = top4_merge(r[q], r[q + w]);
     t = top4_merge(t, r[0]);
   }
   t = top4_wave_reduce(t);
   const float lse = t.m == kNegInf ? kNegInf : t.m + logf(t.s);
+  int top_tok = -1;
   if (lane < kTopK) {
     uint64_t key = t.k[0];
 #pragma unroll
@@ -419,14 +421,16 @@ void k_draft_grow(DraftGrowArgs a) {
     const int id = key_id(key);
     float lp = v - lse;
     lp = lp != lp ? kNegInf : lp;
-    const int tok = a.vocab_map ? a.vocab_map[id] : id;
-    a.topk_id[row * kTopK + lane] = tok;
+    top_tok = a.vocab_map ? a.vocab_map[id] : id;
     a.topk_logp[row * kTopK + lane] = lp;
-    s_id[slot][lane] = tok;
+    s_id[slot][lane] = id;
     s_lp[slot][lane] = lp;
   }
   if (lane == 0) a.row_lse[row] = lse;
   __syncthreads();
+  // the map's entry has a round trip to memory: nobody waits for it at the barrier, and the
+  // growth step reads its own while it ranks
+  if (lane < kTopK) a.topk_id[row * kTopK + lane] = top_tok;
   if (slot != 0) return;
 
   // ---- wave 0: one growth step of request b's tree
@@ -453,6 +457,7 @@ void k_draft_grow(DraftGrowArgs a) {
         }
       sc = __fadd_rn(fs, s_lp[j][c]);
       tok = s_id[j][c];
+      if (a.vocab_map) tok = a.vocab_map[tok];
       par = fp;
     }
     // rank of each candidate: the candidates with a higher score, or an equal score and an
