@@ -385,8 +385,9 @@ int asv_verify_tuned(const asv_verify_args *args, const asv_tuning *tuning, void
                      uint64_t workspace_bytes, void *stream);
 
 /* One launch of the LM-head kernel of asv_verify (see asv_k1_plan). Up to 64 rows the launch cuts
- * its ids anew into narrower slabs, by V and the compute units (cut_rows64 in asv_api.hip); the
- * fields then describe the uncut 256-id slabs. */
+ * its ids anew into narrower slabs, by V and the compute units (cut_rows64 in asv_api.hip), and up
+ * to 512 rows one launch with a tail of narrower slabs takes the place of the plan's where that is
+ * estimated to be faster (cut_wide); the fields then describe the uncut 256-id slabs. */
 typedef struct asv_k1_launch {
   int32_t tile_rows;              /* tree rows per workgroup tile: 64, 128, 192 or 256 */
   int32_t slab0;                  /* first vocabulary slab (256 ids each) of the launch */

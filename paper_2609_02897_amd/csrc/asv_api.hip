@@ -82,7 +82,8 @@ int cu_count() {
   return n;
 }
 
-K1Plan plan_k1(int N, int S, int cus) {
+// est: the plan's estimate (beyond 64 rows).
+K1Plan plan_k1(int N, int S, int cus, int64_t* est_out = nullptr) {
   if (N <= 64) return K1Plan{Tile::kRows64, Tile::kRows64, S};
   struct Family { Tile tile; int rows; int cost; };
   const Family families[3] = {{Tile::kRows128, 128, 62}, {Tile::kRows192, 192, 80},
@@ -118,6 +119,7 @@ K1Plan plan_k1(int N, int S, int cus) {
       }
     }
   }
+  if (est_out) *est_out = best_est;
   return best;
 }
 
@@ -199,10 +201,63 @@ Cut64 cut_rows64(int V, int cus) {
   return Cut64{Stream64::kDeep128, SlabCut{n1, 128, tw, 0, 0}, n1 + (rest + tw - 1) / tw, tail64};
 }
 
+// ---- The cut of the vocabulary from 65 to 512 rows. A last round that 256-id slabs leave partly
+// empty costs as much as a full one, and the plan's second family (more row tiles on the remaining
+// slabs) a second launch and another pass over those slabs. Here the slabs fill whole rounds of
+// one family, and the ids that remain are shared equally among the CUs, one narrower tile each, in
+// the same launch. Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
+// V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 202; 190 rows at 32000 71 -> 61, 81920
+// 149 -> 134, 147456 242 -> 228; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 69632
+// 203 -> 197; 500 rows at 73728 256 -> 247.
+struct CutWide {
+  int rows = 0;    // tree rows of a tile; 0: the plan's whole slabs are no worse
+  int tail_ids;    // ids of the tail's tiles
+  SlabCut cut;
+  int S;           // slabs in all = records per row
+};
+
+constexpr int kMaxCutRows = 512;
+constexpr int kMaxCutTail = 512;    // most slabs of a tail (the workspace holds as many records)
+
+CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
+  CutWide best;
+  if (N <= 64 || N > kMaxCutRows || V > kMaxCutVocab) return best;
+  struct Tail { int ids, cost; };
+  struct Family { int rows, cost; Tail tails[3]; };
+  // one round of tails in the plan's units; measured at 120, 190 and 250 rows after one and two
+  // rounds: 30-34, 38-46 and 52-60 us (128 rows), 32-41, 50-55 and 70-71, 42-52, 57-64 and 85-87
+  const Family families[3] = {{128, 62, {{64, 30}, {128, 44}, {192, 62}}},
+                              {192, 80, {{64, 36}, {128, 54}, {192, 70}}},
+                              {256, 98, {{64, 44}, {128, 70}, {192, 90}}}};
+  int64_t best_est = plan_est;
+  for (const Family& f : families) {
+    const int RT = (N + f.rows - 1) / f.rows, per_round = cus / RT;    // slabs of one round
+    if (RT > 2 || per_round < 1) continue;
+    const int rounds = V / (kSlab * per_round), n_main = rounds * per_round;
+    const int rest = V - n_main * kSlab;
+    for (const Tail& t : f.tails) {
+      const int width = std::max(kMinCut, ((rest + per_round - 1) / per_round + 7) / 8 * 8);
+      const int n_tail = (rest + width - 1) / width;
+      int64_t est = (int64_t)rounds * f.cost + t.cost;
+      // two row tiles: level with the plan where the estimates are within 6% (378 rows at
+      // V = 49152 136 against 134 us, 500 rows at 81920 275 against 265)
+      if (RT == 2) est = est * 53 / 50;
+      if (rest == 0 || width > t.ids || n_tail > kMaxCutTail || est >= best_est) continue;
+      best_est = est;
+      best.rows = f.rows;
+      best.tail_ids = t.ids;
+      best.cut = SlabCut{n_main, kSlab, width, 0, 0};
+      best.S = n_main + n_tail;
+    }
+  }
+  return best;
+}
+
 // Most records per row that a step of N rows writes, whatever the device's CU count.
 int max_records(int N, int V) {
-  const int width = N <= 64 && V <= kMaxCutVocab ? kMinCut : kSlab;
-  return (V + width - 1) / width;
+  const int whole = (V + kSlab - 1) / kSlab;
+  if (N > kMaxCutRows || V > kMaxCutVocab) return whole;
+  return N <= 64 ? (V + kMinCut - 1) / kMinCut : whole + kMaxCutTail;
 }
 
 // Launches of at most this many row tiles copy W with the non-temporal hint (the one or two
@@ -383,6 +438,31 @@ void launch_rows64(const LmheadArgs& g, const Cut64& c, const asv_k1_launch& k, 
     case Stream64::kWide256:
       launch_lmhead<Wide256>(g, c.cut, n_tail, k, s, ev);
       break;
+  }
+}
+
+// The slabs of cut_wide: one launch of the family's 256-id tile, its tail on a narrower one (alone,
+// where the vocabulary holds no whole round).
+template <int TR, int NST, int TAIL_IDS, int TAIL_NST>
+void launch_cut(const LmheadArgs& g, const CutWide& c, hipStream_t s, const K1Events& ev) {
+  using M = TileFamily<kSlab, TR, 2, 2, NST, NST, true>;
+  using T = TileFamily<TAIL_IDS, TR, 2, 2, TAIL_NST, TAIL_NST, true>;
+  asv_k1_launch k{};
+  k.row_tiles = (g.N + TR - 1) / TR;
+  const int n_tail = (c.S - c.cut.n_main) * k.row_tiles;
+  if (c.cut.n_main > 0)
+    launch_lmhead<M, T>(g, c.cut, n_tail, k, s, ev);
+  else
+    launch_lmhead<T>(g, SlabCut{0, kSlab, c.cut.tail_width, 0, 0}, n_tail, k, s, ev);
+}
+
+template <int TR, int NST>
+void launch_cut_rows(const LmheadArgs& g, const CutWide& c, hipStream_t s, const K1Events& ev) {
+  switch (c.tail_ids) {
+    case 64: launch_cut<TR, NST, 64, 3>(g, c, s, ev); break;
+    case 128: launch_cut<TR, NST, 128, 3>(g, c, s, ev); break;
+    // three slots of 192 ids and 256 rows are 168 KB
+    default: launch_cut<TR, NST, 192, TR == 256 ? 2 : 3>(g, c, s, ev); break;
   }
 }
 
@@ -657,18 +737,26 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   }
 
   const int cus = cu_count();
+  int64_t est = 0;           // no cut where the tile is forced
   const K1Plan plan = tu.tile_rows != 0 ? K1Plan{forced, forced, L.S}
-                                         : plan_k1(a->N, L.S, cus);
+                                         : plan_k1(a->N, L.S, cus, &est);
+  const CutWide wide = cut_wide(a->N, a->V, cus, est);
   asv_k1_launch k1[2];
   const int n_k1 = k1_launches(a->N, L.S, cus, plan, k1);
   const bool rows64 = k1[0].tile_rows == 64 && a->N <= 64;
   const Cut64 cut64 = cut_rows64(a->V, cus);
-  const int S = rows64 ? cut64.S : L.S;             // records per row
+  const int S = rows64 ? cut64.S : wide.rows ? wide.S : L.S;             // records per row
   const LmheadArgs g = lmhead_args(a, L, ws, S);
   // timing events (measurement only): the start of the first launch, the end of the last
   const hipEvent_t ev_begin = reinterpret_cast<hipEvent_t>(tu.begin_event);
   const hipEvent_t ev_end = reinterpret_cast<hipEvent_t>(tu.end_event);
-  for (int q = 0; q < n_k1; ++q) {
+  switch (wide.rows) {
+    case 128: launch_cut_rows<128, 3>(g, wide, s, K1Events{ev_begin, ev_end}); break;
+    case 192: launch_cut_rows<192, 2>(g, wide, s, K1Events{ev_begin, ev_end}); break;
+    case 256: launch_cut_rows<256, 2>(g, wide, s, K1Events{ev_begin, ev_end}); break;
+    default: break;
+  }
+  for (int q = 0; q < n_k1 && !wide.rows; ++q) {
     const asv_k1_launch& k = k1[q];
     const K1Events ev{q == 0 ? ev_begin : nullptr, q == n_k1 - 1 ? ev_end : nullptr};
     // <tree rows, waves along vocab, waves along rows, ring depth, K loop>, each the fastest of

@@ -692,8 +692,7 @@ __device__ __forceinline__ void family_tile(
   }
 }
 
-// The tile of workgroup blockIdx.x in a launch over cut's slabs x RT row tiles (RT = 1 when the
-// cut has a tail): consecutive tiles share W slabs and X row tiles through one XCD's L2; the
+// The tile of workgroup blockIdx.x in a launch over cut's slabs x RT row tiles: consecutive tiles share W slabs and X row tiles through one XCD's L2; the
 // tail's tiles are dealt to the XCDs on their own, so that every XCD gets its part of them.
 struct TileAt {
   int v0, v_end, rt, rec;
@@ -704,11 +703,11 @@ __device__ __forceinline__ TileAt tile_at(const SlabCut& cut, int V, int RT, int
   const int main_tiles = cut.n_main * RT, bid = blockIdx.x;
   TileAt t;
   t.tail = bid >= main_tiles;
-  t.rt = 0;
   int slab;
-  if (t.tail)
-    slab = cut.n_main + xcd_tile(bid - main_tiles, gridDim.x - main_tiles);
-  else
+  if (t.tail) {
+    tile_coords(xcd_tile(bid - main_tiles, gridDim.x - main_tiles), 0, RT, 0, 0, slab, t.rt);
+    slab += cut.n_main;
+  } else
     tile_coords(xcd_tile(bid, main_tiles), cut.n_main, RT, blk_slabs, blk_rows, slab, t.rt);
   const int width = t.tail ? cut.tail_width : cut.width;
   t.v0 = cut.v_first +
@@ -926,7 +925,7 @@ void k_lmhead_partial(LmheadArgs a, SlabCut cut, int RT, int blk_slabs, int blk_
     a.done_cnt[i] = 0;
   const TileAt t = tile_at(cut, a.V, RT, blk_slabs, blk_rows);
   if constexpr (!std::is_same_v<M, T>) {
-    if (t.tail) return lmhead_block<T>(a, t.v0, t.v_end, 0, t.rec, smem);
+    if (t.tail) return lmhead_block<T>(a, t.v0, t.v_end, t.rt * T::TR, t.rec, smem);
   }
   lmhead_block<M>(a, t.v0, t.v_end, t.rt * M::TR, t.rec, smem);
 }

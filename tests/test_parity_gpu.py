@@ -731,3 +731,41 @@ def test_rows64_vocabulary_cut(asv, dev, V, sizes):
             assert torch.equal(getattr(got, f), getattr(base, f)), f
         assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
         assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
+
+
+# From 65 to 512 rows: the smallest V of each (row tile, tail width) on 256 CUs, alone and behind
+# whole rounds of 256-id slabs, ends of the row tiles, and sizes that keep the plan's slabs.
+@pytest.mark.parametrize("N,V", [(65, 5), (65, 16385), (128, 32769), (128, 65537), (100, 81921),
+                                 (120, 98305), (129, 16000), (192, 32768), (192, 65600), (150, 90000),
+                                 (192, 98305), (193, 16384), (256, 65536 + 16385), (193, 32769),
+                                 (256, 36864), (256, 40961), (300, 33000), (384, 57344),
+                                 (385, 34000), (512, 36864), (513, 34000), (70, 262145)])
+def test_wide_vocabulary_cut(asv, dev, N, V):
+    """From 65 to 512 rows the ids beyond whole rounds go to one tail of narrower slabs. Against
+    the plan's whole slabs (a forced tile), on both weight layouts, as in the test above."""
+    import torch
+    print(f"[wide cut] N={N} V={V}", flush=True)
+    H = 64
+    g = torch.Generator(device=dev)
+    g.manual_seed(V + N)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    w = torch.empty((V, H), **bf).normal_(0, 0.1, generator=g)
+    w[V - 1] = w[0]                                   # an exact tie of the first and the last id
+    hidden = torch.empty((N, H), **bf).normal_(0, 1, generator=g)
+    off = np.array([0, N // 3, N // 2, N], np.int32)
+    parent = np.concatenate([np.r_[-1, lo + np.arange(hi - lo - 1) // 2]
+                             for lo, hi in zip(off, off[1:])]).astype(np.int32)
+    tok = torch.randint(0, V, (N,), dtype=torch.int32, device=dev, generator=g)
+    args = (tok, torch.from_numpy(parent).to(dev), torch.from_numpy(off).to(dev),
+            torch.full((3,), 0.2, device=dev))
+    base = asv.verify(hidden, w, *args, k1_tile=128)
+    nonroot = torch.from_numpy(parent >= 0).to(dev)
+    ws = asv.alloc_workspace(3, N, H, V, dev)
+    for weight in (w, asv.pack_lm_head(w)):
+        ws.fill_(0x7f)                                # records left unwritten would be seen
+        got = asv.verify(hidden, weight, *args, workspace=ws)
+        for f in ("row_max", "row_argmax", "accept", "accepted_len", "accepted_path",
+                  "bonus_token", "req_status"):
+            assert torch.equal(getattr(got, f), getattr(base, f)), f
+        assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
+        assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
