@@ -205,18 +205,22 @@ Cut64 cut_rows64(int V, int cus) {
 // empty costs as much as a full one, and the plan's second family (more row tiles on the remaining
 // slabs) a second launch and another pass over those slabs. Here the slabs fill whole rounds of
 // one family, and the ids that remain are shared equally among the CUs, one narrower tile each, in
-// the same launch. Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
-// V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 202; 190 rows at 32000 71 -> 61, 81920
-// 149 -> 134, 147456 242 -> 228; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 69632
-// 203 -> 197; 500 rows at 73728 256 -> 247.
+// the same launch. Behind two rounds and more the tail's slabs stay 256 ids wide, on 64-row tiles
+// (each reads its W through the L2 of the slab's XCD): level with the narrower slabs there (190
+// rows at V = 151936, with the policy 254 -> 250 us), and the records, and with them row_lse, are the plan's bit for bit.
+// Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
+// V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 213; 190 rows at 32000 71 -> 61, 81920
+// 149 -> 134, 147456 242 -> 233; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 36864
+// 122 -> 119; 500 rows at 40960 157 -> 151.
 struct CutWide {
   int rows = 0;    // tree rows of a tile; 0: the plan's whole slabs are no worse
-  int tail_ids;    // ids of the tail's tiles
+  int tail_ids, tail_rows;    // ids and tree rows of the tail's tiles
   SlabCut cut;
   int S;           // slabs in all = records per row
 };
 
 constexpr int kMaxCutRows = 512;
+constexpr int kRows64Cost = 44;     // a round of 256 ids x 64 rows behind others, in the plan's units
 constexpr int kMaxCutTail = 512;    // most slabs of a tail (the workspace holds as many records)
 
 CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
@@ -226,7 +230,7 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
   struct Family { int rows, cost; Tail tails[3]; };
   // one round of tails in the plan's units; measured at 120, 190 and 250 rows after one and two
   // rounds: 30-34, 38-46 and 52-60 us (128 rows), 32-41, 50-55 and 70-71, 42-52, 57-64 and 85-87
-  const Family families[3] = {{128, 62, {{64, 30}, {128, 44}, {192, 62}}},
+  const Family families[3] = {{128, 62, {{64, 30}, {128, 44}, {192, 60}}},
                               {192, 80, {{64, 36}, {128, 54}, {192, 70}}},
                               {256, 98, {{64, 44}, {128, 70}, {192, 90}}}};
   int64_t best_est = plan_est;
@@ -242,12 +246,24 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
       // two row tiles: level with the plan where the estimates are within 6% (378 rows at
       // V = 49152 136 against 134 us, 500 rows at 81920 275 against 265)
       if (RT == 2) est = est * 53 / 50;
-      if (rest == 0 || width > t.ids || n_tail > kMaxCutTail || est >= best_est) continue;
+      if (rounds > 1 || rest == 0 || width > t.ids || n_tail > kMaxCutTail || est >= best_est)
+        continue;
       best_est = est;
-      best.rows = f.rows;
+      best.rows = best.tail_rows = f.rows;
       best.tail_ids = t.ids;
       best.cut = SlabCut{n_main, kSlab, width, 0, 0};
       best.S = n_main + n_tail;
+    }
+    const int slabs = (rest + kSlab - 1) / kSlab, tail_RT = (N + 63) / 64;
+    const int64_t est = (int64_t)rounds * f.cost +
+                        ((int64_t)slabs * tail_RT + cus - 1) / cus * kRows64Cost;
+    if (rounds > 1 && rest > 0 && est < best_est) {
+      best_est = est;
+      best.rows = f.rows;
+      best.tail_rows = 64;
+      best.tail_ids = kSlab;
+      best.cut = SlabCut{n_main, kSlab, kSlab, 0, 0};
+      best.S = n_main + slabs;
     }
   }
   return best;
@@ -401,7 +417,7 @@ struct K1Events {
   hipEvent_t start, stop;
 };
 
-// The tiles of `cut` (n_tail slabs in its tail) x k.row_tiles on families M and T.
+// The main slabs of `cut` x k.row_tiles on family M and its tail's n_tail tiles on family T.
 template <class M, class T = M>
 void launch_lmhead(const LmheadArgs& g, const SlabCut& cut, int n_tail, const asv_k1_launch& k,
                    hipStream_t s, const K1Events& ev) {
@@ -458,6 +474,13 @@ void launch_cut(const LmheadArgs& g, const CutWide& c, hipStream_t s, const K1Ev
 
 template <int TR, int NST>
 void launch_cut_rows(const LmheadArgs& g, const CutWide& c, hipStream_t s, const K1Events& ev) {
+  if (c.tail_rows == 64) {
+    using M = TileFamily<kSlab, TR, 2, 2, NST, NST, true>;
+    asv_k1_launch k{};
+    k.row_tiles = (g.N + TR - 1) / TR;
+    launch_lmhead<M, Spread256>(g, c.cut, (c.S - c.cut.n_main) * ((g.N + 63) / 64), k, s, ev);
+    return;
+  }
   switch (c.tail_ids) {
     case 64: launch_cut<TR, NST, 64, 3>(g, c, s, ev); break;
     case 128: launch_cut<TR, NST, 128, 3>(g, c, s, ev); break;

@@ -300,7 +300,7 @@ __global__ __launch_bounds__(M::C::kThreads, 1)
 void k_draft_partial(DraftArgs a, SlabCut cut, int RT) {
   static_assert(M::C::kThreads == T::C::kThreads && M::TR == T::TR, "one workgroup shape");
   __shared__ uint4 smem[(M::C::kLds > T::C::kLds ? M::C::kLds : T::C::kLds) / 16];
-  const TileAt t = tile_at(cut, a.V, RT, 0, 0);
+  const TileAt t = tile_at(cut, a.V, RT, RT, 0, 0);
   if constexpr (!std::is_same_v<M, T>) {
     if (t.tail) return draft_block<T>(a, t.v0, t.v_end, 0, t.rec, smem);
   }

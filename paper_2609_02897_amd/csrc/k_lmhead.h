@@ -692,20 +692,22 @@ __device__ __forceinline__ void family_tile(
   }
 }
 
-// The tile of workgroup blockIdx.x in a launch over cut's slabs x RT row tiles: consecutive tiles share W slabs and X row tiles through one XCD's L2; the
+// The tile of workgroup blockIdx.x in a launch over cut's slabs x RT row tiles (tail_RT in its
+// tail): consecutive tiles share W slabs and X row tiles through one XCD's L2; the
 // tail's tiles are dealt to the XCDs on their own, so that every XCD gets its part of them.
 struct TileAt {
   int v0, v_end, rt, rec;
   bool tail;
 };
-__device__ __forceinline__ TileAt tile_at(const SlabCut& cut, int V, int RT, int blk_slabs,
-                                          int blk_rows) {
+__device__ __forceinline__ TileAt tile_at(const SlabCut& cut, int V, int RT, int tail_RT,
+                                          int blk_slabs, int blk_rows) {
   const int main_tiles = cut.n_main * RT, bid = blockIdx.x;
   TileAt t;
   t.tail = bid >= main_tiles;
   int slab;
   if (t.tail) {
-    tile_coords(xcd_tile(bid - main_tiles, gridDim.x - main_tiles), 0, RT, 0, 0, slab, t.rt);
+    tile_coords(xcd_tile(bid - main_tiles, gridDim.x - main_tiles), 0, tail_RT, 0, 0, slab,
+                t.rt);
     slab += cut.n_main;
   } else
     tile_coords(xcd_tile(bid, main_tiles), cut.n_main, RT, blk_slabs, blk_rows, slab, t.rt);
@@ -917,13 +919,14 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
 template <class M, class T>
 __global__ __launch_bounds__(M::C::kThreads, 1)
 void k_lmhead_partial(LmheadArgs a, SlabCut cut, int RT, int blk_slabs, int blk_rows) {
-  static_assert(M::C::kThreads == T::C::kThreads && M::TR == T::TR, "one workgroup shape");
+  static_assert(M::C::kThreads == T::C::kThreads, "one workgroup shape");
   __shared__ uint4 smem[(M::C::kLds > T::C::kLds ? M::C::kLds : T::C::kLds) / 16];
   // clear the per-request completion counters of the finishing kernel that follows
   for (int i = blockIdx.x * M::C::kThreads + threadIdx.x; i < a.n_cnt;
        i += gridDim.x * M::C::kThreads)
     a.done_cnt[i] = 0;
-  const TileAt t = tile_at(cut, a.V, RT, blk_slabs, blk_rows);
+  const TileAt t = tile_at(cut, a.V, RT, M::TR == T::TR ? RT : (a.N + T::TR - 1) / T::TR, blk_slabs,
+                           blk_rows);
   if constexpr (!std::is_same_v<M, T>) {
     if (t.tail) return lmhead_block<T>(a, t.v0, t.v_end, t.rt * T::TR, t.rec, smem);
   }

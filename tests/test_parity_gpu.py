@@ -739,9 +739,11 @@ def test_rows64_vocabulary_cut(asv, dev, V, sizes):
                                  (120, 98305), (129, 16000), (192, 32768), (192, 65600), (150, 90000),
                                  (192, 98305), (193, 16384), (256, 65536 + 16385), (193, 32769),
                                  (256, 36864), (256, 40961), (300, 33000), (384, 57344),
-                                 (385, 34000), (512, 36864), (513, 34000), (70, 262145)])
+                                 (385, 34000), (512, 36864), (513, 34000), (70, 262145),
+                                 (90, 131072 + 255), (190, 151936), (256, 140000), (230, 65700)])
 def test_wide_vocabulary_cut(asv, dev, N, V):
-    """From 65 to 512 rows the ids beyond whole rounds go to one tail of narrower slabs. Against
+    """From 65 to 512 rows the ids beyond whole rounds go to one tail of narrower slabs or, behind
+    two rounds, of 64-row tiles. Against
     the plan's whole slabs (a forced tile), on both weight layouts, as in the test above."""
     import torch
     print(f"[wide cut] N={N} V={V}", flush=True)
