@@ -751,14 +751,6 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   const bool conf = a->draft_logits != nullptr;
   (void)hipGetLastError();
 
-  // K4 first: it only needs the inputs and overlaps nothing it depends on.
-  if (conf) {
-    k_draft_conf_partial<<<dim3(L.n_conf, a->B), kConfThreads, 0, s>>>(
-        a->N, a->V, a->req_offsets, a->draft_logits, reinterpret_cast<float*>(ws + L.off_conf_m),
-        reinterpret_cast<float*>(ws + L.off_conf_s));
-    if (int rc = launch_status("k_draft_conf_partial")) return rc;
-  }
-
   const int cus = cu_count();
   int64_t est = 0;           // no cut where the tile is forced
   const K1Plan plan = tu.tile_rows != 0 ? K1Plan{forced, forced, L.S}
@@ -769,7 +761,21 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   const bool rows64 = k1[0].tile_rows == 64 && a->N <= 64;
   const Cut64 cut64 = cut_rows64(a->V, cus);
   const int S = rows64 ? cut64.S : wide.rows ? wide.S : L.S;             // records per row
-  const LmheadArgs g = lmhead_args(a, L, ws, S);
+  LmheadArgs g = lmhead_args(a, L, ws, S);
+  // K4 only needs the inputs: up to 64 rows its shares go to K1's tiles, one each, which saves its
+  // launch (8 rows at V = 128256, one request: 165.6 -> 162.9 us), where there are enough tiles
+  g.conf = ConfArgs{a->N, a->V, a->req_offsets, a->draft_logits,
+                    reinterpret_cast<float*>(ws + L.off_conf_m),
+                    reinterpret_cast<float*>(ws + L.off_conf_s), L.n_conf, 0};
+  const int64_t shares = conf ? (int64_t)conf_shares(L.n_conf) * a->B : 0;
+  if (rows64 && shares <= cut64.S) {
+    g.conf.n_shares = (int)shares;
+  } else if (conf) {
+    ConfArgs c = g.conf;
+    c.n_shares = (int)std::min<int64_t>(shares, INT32_MAX);
+    k_draft_conf_partial<<<dim3(conf_shares(L.n_conf), a->B), kConfWaves * kWave, 0, s>>>(c);
+    if (int rc = launch_status("k_draft_conf_partial")) return rc;
+  }
   // timing events (measurement only): the start of the first launch, the end of the last
   const hipEvent_t ev_begin = reinterpret_cast<hipEvent_t>(tu.begin_event);
   const hipEvent_t ev_end = reinterpret_cast<hipEvent_t>(tu.end_event);

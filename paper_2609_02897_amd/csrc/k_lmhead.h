@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "k_common.h"
+#include "k_reduce.h"
 
 namespace asv {
 
@@ -645,6 +646,7 @@ struct LmheadArgs {
   int32_t* done_cnt;             // n_cnt counters of the finishing kernel, cleared here
   int n_cnt;
   int w_packed;                  // 0: W row-major; else packed, V rounded up to this many rows
+  ConfArgs conf;                 // the draft logits' records that 64-row tiles also write
 };
 
 // How a launch cuts the vocabulary into the tiles' slabs: slabs [0, n_main) of `width` ids, then
@@ -760,6 +762,16 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
       cp[k] = parent[cc[k]];
       cd[k] = draft_tok[cc[k]];
     }
+  }
+
+  // ---- the tile's share of the draft logits, loaded here and reduced at the end. 64-row tiles
+  // only: the larger ones have no registers to keep it in (loaded after the K loop instead, the
+  // 256-row tile spilled: 3048 rows 2779 -> 2893 us, 190 and 378 rows level).
+  static_assert(C::kWaves == kConfWaves, "a workgroup's waves take a share's records");
+  ConfShare conf;
+  if constexpr (TR == 64) {
+    conf.begin(a.conf, blockIdx.x, wave);
+    conf.load(a.conf, lane);
   }
 
   // ---- the tile's logits
@@ -913,6 +925,7 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
       a.rec_a[at] = r.a;
     }
   }
+  if constexpr (TR == 64) conf.finish(a.conf, lane);
 }
 
 // A launch of K1: the tiles of cut's slabs x RT row tiles on family M, the tail's on family T.

@@ -6,56 +6,84 @@
 
 namespace asv {
 
-constexpr int kConfPerThread = 8;
-constexpr int kConfThreads = 256;
-constexpr int kConfChunk = kConfPerThread * kConfThreads;   // draft logits per K4 workgroup
+constexpr int kConfPerLane = 32;
+constexpr int kConfChunk = kConfPerLane * kWave;   // draft logits per record, one wave each
+constexpr int kConfWaves = 4;                      // records per workgroup
 
-// Grid (chunks, B). Workgroup (ch, b) reduces draft_logits[root_b][ch*kConfChunk ...] to one
-// (max, sum of exp(q - max)) record in one pass: each thread issues its eight loads (entry
-// lo + 256 i + t, coalesced per wave) before using any, then reduces them in registers.
-// Entries past V read as -inf and add nothing. An out-of-range root (malformed offsets,
-// reported by K3) yields an empty record and reads nothing.
-__global__ __launch_bounds__(kConfThreads)
-void k_draft_conf_partial(int N, int V, const int32_t* __restrict__ req_offsets,
-                          const float* __restrict__ q, float* __restrict__ part_m,
-                          float* __restrict__ part_s) {
-  __shared__ float sm[kConfThreads / kWave], ss[kConfThreads / kWave];
-  const int ch = blockIdx.x, b = blockIdx.y, nch = gridDim.x;
-  const int root = req_offsets[b];
-  const int lo = ch * kConfChunk, hi = min(lo + kConfChunk, V);
-  Rec r = rec_empty();
-  if (root >= 0 && root < N) {
-    const float* row = q + (size_t)root * V;
-    float x[kConfPerThread];
+struct ConfArgs {
+  int N, V;
+  const int32_t* req_offsets;
+  const float* q;       // draft logits [N][V]
+  float* part_m;
+  float* part_s;
+  int n_conf;           // records per request
+  int n_shares;         // shares of the launch (0: none): K1's tile t takes share t
+};
+
+__host__ __device__ __forceinline__ int conf_shares(int n_conf) {   // workgroups per request
+  return (n_conf + kConfWaves - 1) / kConfWaves;
+}
+
+// Share i of a launch: wave w reduces chunk 4 (i mod shares) + w of request i / shares to one (max,
+// sum of exp(q - max)) record in one pass: each lane issues its loads (entry lo + 64 k + lane,
+// coalesced) before using any, then reduces them in registers. Entries past V read as -inf and
+// add nothing. An out-of-range root (malformed offsets, reported by K3) yields an empty record
+// and reads nothing. The three parts may lie apart, so that other work covers the loads.
+struct ConfShare {
+  int b, ch, root, lo, hi;
+  bool mine;            // the wave has a record to write
+  float x[kConfPerLane];
+
+  __device__ __forceinline__ void begin(const ConfArgs& a, int i, int wave) {
+    const int shares = conf_shares(a.n_conf);
+    b = i / shares;
+    ch = (i % shares) * kConfWaves + wave;
+    mine = i < a.n_shares && ch < a.n_conf;
+    if (!mine) return;
+    root = a.req_offsets[b];
+    lo = ch * kConfChunk;
+    hi = min(lo + kConfChunk, a.V);
+  }
+  __device__ __forceinline__ bool readable(const ConfArgs& a) const {
+    return root >= 0 && root < a.N;
+  }
+  __device__ __forceinline__ void load(const ConfArgs& a, int lane) {
+    if (!mine || !readable(a)) return;
+    const float* row = a.q + (size_t)root * a.V;
 #pragma unroll
-    for (int i = 0; i < kConfPerThread; ++i) {
-      const int v = lo + i * kConfThreads + (int)threadIdx.x;
-      x[i] = v < hi ? row[v] : kNegInf;
+    for (int k = 0; k < kConfPerLane; ++k) x[k] = row[min(lo + k * kWave + lane, hi - 1)];
+  }
+  __device__ __forceinline__ void finish(const ConfArgs& a, int lane) {
+    if (!mine) return;
+    float m = kNegInf, s = 0.f;
+    if (readable(a)) {
+#pragma unroll
+      for (int k = 0; k < kConfPerLane; ++k) {
+        x[k] = lo + k * kWave + lane < hi ? x[k] : kNegInf;
+        m = fmaxf(m, x[k]);
+      }
+      if (m != kNegInf) {
+        const float mb = m * kLog2e;
+#pragma unroll
+        for (int k = 0; k < kConfPerLane; ++k) s += exp2_rel(fmaf(x[k], kLog2e, -mb));
+      }
     }
-    float m = x[0];
-#pragma unroll
-    for (int i = 1; i < kConfPerThread; ++i) m = fmaxf(m, x[i]);
-    float s = 0.f;
-    if (m != kNegInf) {
-      const float mb = m * kLog2e;
-#pragma unroll
-      for (int i = 0; i < kConfPerThread; ++i) s += exp2_rel(fmaf(x[i], kLog2e, -mb));
+    const Rec r = rec_wave_reduce_dpp(Rec{m, s, 0});   // all -inf: m = -inf, s = 0
+    if (lane == 0) {
+      a.part_m[(size_t)b * a.n_conf + ch] = r.m;
+      a.part_s[(size_t)b * a.n_conf + ch] = r.s;
     }
-    r = Rec{m, s, 0};
   }
-  r = rec_wave_reduce(r);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) {
-    sm[w] = r.m;
-    ss[w] = r.s;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    Rec t{sm[0], ss[0], 0};
-    for (int i = 1; i < kConfThreads / kWave; ++i) t = rec_merge(t, Rec{sm[i], ss[i], 0});
-    part_m[(size_t)b * nch + ch] = t.m;
-    part_s[(size_t)b * nch + ch] = t.s;
-  }
+};
+
+// A launch of its own, one workgroup per share.
+__global__ __launch_bounds__(kConfWaves * kWave)
+void k_draft_conf_partial(ConfArgs a) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  ConfShare c;
+  c.begin(a, blockIdx.y * gridDim.x + blockIdx.x, wave);
+  c.load(a, lane);
+  c.finish(a, lane);
 }
 
 }  // namespace asv

@@ -771,3 +771,36 @@ def test_wide_vocabulary_cut(asv, dev, N, V):
             assert torch.equal(getattr(got, f), getattr(base, f)), f
         assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
         assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
+
+
+# Draft logits in K1's tiles (up to 64 rows, while its slabs outnumber the 8192-logit shares) and in
+# a launch of their own: one share and its remainders, several, more requests than slabs, 65 rows.
+@pytest.mark.parametrize("V,sizes", [(5, (1,)), (2049, (3, 2)), (8192, (8,)), (8193, (8, 8)),
+                                     (20000, (2,) * 32), (300, (1,) * 40), (8193, (30, 35))])
+def test_draft_confidence_shares(asv, dev, V, sizes):
+    """draft_conf against float64 softmax: each float32 term's relative error is at most 2^-20 for
+    |q - max| < 16, their sum's a few 2^-24 more. A row of -inf but one entry has confidence 1."""
+    import torch
+    print(f"[conf] V={V} sizes={sizes}", flush=True)
+    H, N, B = 64, sum(sizes), len(sizes)
+    g = torch.Generator(device=dev)
+    g.manual_seed(V + N)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    w = torch.empty((V, H), **bf).normal_(0, 0.1, generator=g)
+    hidden = torch.empty((N, H), **bf).normal_(0, 1, generator=g)
+    q = torch.empty((N, V), device=dev).normal_(0, 2, generator=g)
+    off = np.cumsum((0,) + sizes).astype(np.int32)
+    q[int(off[B - 1])] = -float("inf")
+    q[int(off[B - 1]), V - 1] = 3.0
+    parent = np.concatenate([np.r_[-1, lo + np.arange(n - 1) // 2]
+                             for lo, n in zip(off, sizes)]).astype(np.int32)
+    out = asv.alloc_outputs(B, N, dev, True)
+    ws = asv.alloc_workspace(B, N, H, V, dev)
+    ws.fill_(0x7f)                                    # records left unwritten would be seen
+    asv.verify(hidden, w, torch.zeros(N, dtype=torch.int32, device=dev),
+               torch.from_numpy(parent).to(dev), torch.from_numpy(off).to(dev),
+               torch.full((B,), 0.2, device=dev), q, state=asv.state_init(B, device=dev), out=out,
+               workspace=ws)
+    want = torch.softmax(q[torch.from_numpy(off[:-1]).long().to(dev)].double(), 1).max(1)[0]
+    assert ((out.draft_conf - want).abs() / want).max() < 4e-6
+    assert out.draft_conf[B - 1] == 1.0
