@@ -27,6 +27,22 @@ __device__ __forceinline__ Rec rec_empty() { return Rec{kNegInf, 0.f, kNoIndex};
 // sum of such terms (at least one of which is 1) by less than 2^-126 relative.
 __device__ __forceinline__ float exp2_rel(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The largest of two and of five floats, a non-number being the lowest: the compiler first brings
+// every operand of fmaxf into canonical form, an instruction more for each value that comes out of
+// a matrix instruction.
+__device__ __forceinline__ float max_raw(float a, float b) {
+  float r;
+  asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float max5_raw(float a, float b, float c, float d, float e) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3\n\tv_max3_f32 %0, %0, %4, %5"
+      : "=&v"(r)
+      : "v"(a), "v"(b), "v"(c), "v"(d), "v"(e));
+  return r;
+}
+
 // Merge two records; the argmax keeps the lowest index among equal maxima.
 __device__ __forceinline__ Rec rec_merge(Rec x, Rec y) {
   Rec r;
@@ -63,17 +79,6 @@ __device__ __forceinline__ void lane_halves(uint32_t x, uint32_t& first, uint32_
     first = r[0];
     second = r[1];
   }
-}
-
-// The merge of the records that the lanes l, l ^ STEP hold, lower lane first; both get it.
-template <int STEP>
-__device__ __forceinline__ Rec rec_merge_lanes(Rec x) {
-  uint32_t m[2], s[2], a[2];
-  lane_halves<STEP>(__float_as_uint(x.m), m[0], m[1]);
-  lane_halves<STEP>(__float_as_uint(x.s), s[0], s[1]);
-  lane_halves<STEP>((uint32_t)x.a, a[0], a[1]);
-  return rec_merge(Rec{__uint_as_float(m[0]), __uint_as_float(s[0]), (int)a[0]},
-                   Rec{__uint_as_float(m[1]), __uint_as_float(s[1]), (int)a[1]});
 }
 
 // Full-wave reduction; every lane ends with the merged record.

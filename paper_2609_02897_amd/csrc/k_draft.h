@@ -100,7 +100,7 @@ __device__ __forceinline__ Top4 top4_merge(const Top4& a, const Top4& b) {
   return c;
 }
 
-// The merge of the records that the lanes l, l ^ STEP hold (rec_merge_lanes); both get it.
+// The merge of the records that the lanes l, l ^ STEP hold; both get it.
 template <int STEP>
 __device__ __forceinline__ Top4 top4_merge_lanes(const Top4& x) {
   Top4 t[2];

@@ -859,50 +859,80 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
     __syncthreads();
   }
 
-  // ---- per-row slab record: lane-local pass, then the lane groups that hold the same tree
-  // rows (64 / kBlock of them), then the waves that share the same tree rows (through LDS).
-  // Within a lane the entries of a tree row are visited in increasing vocabulary order, so
-  // "strictly greater" keeps the lowest argmax; the argmax is tracked as the entry ordinal
-  // k = kRegs i + e and turned into a vocabulary id afterwards, and merges keep the lowest id
-  // among equal maxima. Only a wave whose ids reach past v_end needs the mask. One row block at a time keeps
-  // the accumulator reads short-lived (sched_barrier stops the scheduler from hoisting them).
+  // ---- per-row slab record: the maximum of the wave's entries of a tree row first (lane-local,
+  // then over the four lane groups that hold the same tree row), then the exponentials and the
+  // lowest argmax against it, summed over the lane groups, then the waves that share the same
+  // tree rows (through LDS). The argmax is tracked as the entry ordinal k = kRegs i + e, taken in
+  // descending order so that the lowest id is kept, and turned into a vocabulary id afterwards;
+  // merges keep the lowest id among equal maxima. Only a wave whose ids reach past v_end needs the
+  // mask. One row block at a time keeps the accumulator reads short-lived (sched_barrier stops the
+  // scheduler from hoisting them). With one wave per SIMD the instruction count bounds this part:
+  // 9.5 issue slots an entry (read, half a max3, fma, the exponential's four, add, compare,
+  // select) against 11 and more with a running argmax and canonical maxima: 2048 rows 1546 -> 1529
+  // us, 3048 rows 2746 -> 2716
+  static_assert(kBlock == 16, "the lane groups of a tree row are the wave's four 16-lane rows");
   const int vwave = v0 + wv * C::kWaveV;
   const bool full = vwave + C::kWaveV <= v_end;
   auto entry_v = [&](int k) {
     return vwave + kBlock * (k / kRegs) + MF::row_of(lane, k % kRegs);
   };
-  // Branch-free lane-local record of row block j; MASK drops entries past v_end.
+  constexpr int kEntries = C::MV * kRegs;
+  static_assert(kEntries % 4 == 0, "entries in groups of four");
+  // Branch-free record of row block j over the wave's ids; MASK drops entries past v_end.
   auto row_record = [&](int j, auto mask_tag) -> Rec {
     constexpr bool MASK = decltype(mask_tag)::value;
+    auto entry = [&](int k) {
+      const float z = acc[k / kRegs][j][k % kRegs];
+      if constexpr (MASK) return entry_v(k) < v_end ? z : kNegInf;
+      else return z;
+    };
     float m = kNegInf;
-    int kbest = 0;
 #pragma unroll
-    for (int i = 0; i < C::MV; ++i)
-#pragma unroll
-      for (int e = 0; e < kRegs; ++e) {
-        const int k = kRegs * i + e;
-        float z = acc[i][j][e];
-        if constexpr (MASK) z = entry_v(k) < v_end ? z : kNegInf;
-        kbest = z > m ? k : kbest;
-        m = fmaxf(m, z);
-      }
+    for (int k = 0; k < kEntries; k += 4)
+      m = max5_raw(m, entry(k), entry(k + 1), entry(k + 2), entry(k + 3));
+    uint32_t lo, hi;
+    lane_halves<16>(__float_as_uint(m), lo, hi);
+    m = max_raw(__uint_as_float(lo), __uint_as_float(hi));
+    lane_halves<32>(__float_as_uint(m), lo, hi);
+    m = max_raw(__uint_as_float(lo), __uint_as_float(hi));
     const float mb = m * kLog2e;
     float sum = 0.f;
+    int kbest = -1;
+    // groups of four, comparisons, exponentials, selects and adds apart: left to itself the compiler
+    // puts each select right behind its comparison and has it wait two slots for the result
 #pragma unroll
-    for (int i = 0; i < C::MV; ++i)
+    for (int g = kEntries - 4; g >= 0; g -= 4) {
+      float t[4];
+      uint64_t best[4];
 #pragma unroll
-      for (int e = 0; e < kRegs; ++e) {
-        const float t = exp2_rel(fmaf(acc[i][j][e], kLog2e, -mb));
-        if constexpr (MASK) sum += entry_v(kRegs * i + e) < v_end ? t : 0.f;
-        else sum += t;
+      for (int q = 3; q >= 0; --q) {
+        const float z = entry(g + q);
+        t[q] = fmaf(z, kLog2e, -mb);
+        best[q] = __builtin_amdgcn_ballot_w64(z == m);
       }
-    return Rec{m, m == kNegInf ? 0.f : sum, m == kNegInf ? kNoIndex : entry_v(kbest)};
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 3; q >= 0; --q) t[q] = exp2_rel(t[q]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 3; q >= 0; --q) 
+        kbest = __builtin_amdgcn_inverse_ballot_w64(best[q]) ? g + q : kbest;
+      sum += (t[0] + t[1]) + (t[2] + t[3]);
+    }
+    int a = kbest < 0 ? kNoIndex : entry_v(kbest);
+    lane_halves<16>(__float_as_uint(sum), lo, hi);
+    sum = __uint_as_float(lo) + __uint_as_float(hi);
+    lane_halves<32>(__float_as_uint(sum), lo, hi);
+    sum = __uint_as_float(lo) + __uint_as_float(hi);
+    lane_halves<16>((uint32_t)a, lo, hi);
+    a = min((int)lo, (int)hi);
+    lane_halves<32>((uint32_t)a, lo, hi);
+    a = min((int)lo, (int)hi);
+    return Rec{m, m == kNegInf ? 0.f : sum, m == kNegInf ? kNoIndex : a};
   };
 #pragma unroll
   for (int j = 0; j < C::MR; ++j) {
-    Rec r = full ? row_record(j, std::false_type{}) : row_record(j, std::true_type{});
-    static_assert(kBlock == 16, "the lane groups of a tree row are the wave's four 16-lane rows");
-    r = rec_merge_lanes<32>(rec_merge_lanes<16>(r));
+    const Rec r = full ? row_record(j, std::false_type{}) : row_record(j, std::true_type{});
     if (lane < kBlock) {
       const int row = wr * C::kWaveR + kBlock * j + lane;
       red_m[wv * TR + row] = r.m;
