@@ -151,13 +151,13 @@ def _need_workspace(ws, need: int, device):
 
 def _need(t, name, dtype, shape):
     import torch
-    if t is None or not isinstance(t, torch.Tensor):
+    if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name}: expected a torch tensor")
-    if t.device.type != "cuda":
+    if not t.is_cuda:
         raise ValueError(f"{name}: must be on a GPU (no CPU path exists)")
     if t.dtype != dtype:
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:                  # torch.Size is a tuple
         raise ValueError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
     if not t.is_contiguous():
         raise ValueError(f"{name}: must be contiguous")
@@ -488,11 +488,11 @@ def commit(req_offsets, draft_tok, accepted_len, accepted_path, bonus_token, row
     a.bonus_token = bonus_token.data_ptr()
     a.commit_off, a.commit_tok, a.commit_row = c_off.data_ptr(), c_tok.data_ptr(), c_row.data_ptr()
     if row_src is not None:
-        if row_src.device.type != "cuda" or not row_src.is_contiguous() or row_src.shape[0] != N:
+        if not row_src.is_cuda or not row_src.is_contiguous() or row_src.shape[0] != N:
             raise ValueError("row_src: a contiguous GPU tensor with N rows")
         dst = torch.empty_like(row_src)
         a.row_src, a.row_dst = row_src.data_ptr(), dst.data_ptr()
-        a.row_bytes = row_src[0].numel() * row_src.element_size() if N else 4
+        a.row_bytes = row_src.numel() // N * row_src.element_size() if N else 4
     a.req_status = status.data_ptr()
     _check(load().asv_commit(ctypes.byref(a), _stream_handle(dev)))
     return c_off, c_tok, c_row, dst, status
