@@ -206,8 +206,9 @@ Cut64 cut_rows64(int V, int cus) {
 // slabs) a second launch and another pass over those slabs. Here the slabs fill whole rounds of
 // one family, and the ids that remain are shared equally among the CUs, one narrower tile each, in
 // the same launch. Behind two rounds and more the tail's slabs stay 256 ids wide, on 64-row tiles
-// (each reads its W through the L2 of the slab's XCD): level with the narrower slabs there (190
-// rows at V = 151936, with the policy 254 -> 250 us), and the records, and with them row_lse, are the plan's bit for bit.
+// (they share each W slab through an XCD's L2): level with the narrower slabs there (190 rows at
+// V = 151936, with the policy 254 -> 250 us), and the records, and with them row_lse, are the plan's
+// bit for bit.
 // Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
 // V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 213; 190 rows at 32000 71 -> 61, 81920
 // 149 -> 134, 147456 242 -> 233; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 36864
