@@ -121,8 +121,10 @@ typedef struct asv_verify_args {
   const float    *draft_logits;   /* [N][V] fp32 draft-model logits, or NULL. Only each
                                      request's root row is read (Eq. (2)). */
   /* outputs, all [N] unless noted */
-  float   *row_max;               /* max_v z_n[v] of row n */
-  float   *row_lse;               /* log sum_v exp(z_n[v]) of row n */
+  float   *row_max;               /* max_v z_n[v] of row n; logits that are no numbers are
+                                     passed over, here and in row_argmax */
+  float   *row_lse;               /* log sum_v exp(z_n[v]) of row n; no number, or the sum over
+                                     the other logits, where one of them is no number */
   int32_t *row_argmax;            /* lowest v attaining row_max */
   float   *drafted_logit;         /* z_{parent(c)}[draft_tok[c]]; roots: unspecified */
   uint8_t *accept;                /* Eq. (1) verdict of each node (1 = accept); roots 1 */

@@ -890,6 +890,8 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
 #pragma unroll
     for (int k = 0; k < kEntries; k += 4)
       m = max5_raw(m, entry(k), entry(k + 1), entry(k + 2), entry(k + 3));
+    // a lane that holds nothing above -inf (all its entries masked, -inf or no numbers) adds nothing
+    const bool empty = m == kNegInf;
     uint32_t lo, hi;
     lane_halves<16>(__float_as_uint(m), lo, hi);
     m = max_raw(__uint_as_float(lo), __uint_as_float(hi));
@@ -915,10 +917,11 @@ __device__ __forceinline__ void lmhead_block(const LmheadArgs& a, int v0, int v_
       for (int q = 3; q >= 0; --q) t[q] = exp2_rel(t[q]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int q = 3; q >= 0; --q) 
+      for (int q = 3; q >= 0; --q)
         kbest = __builtin_amdgcn_inverse_ballot_w64(best[q]) ? g + q : kbest;
       sum += (t[0] + t[1]) + (t[2] + t[3]);
     }
+    sum = empty ? 0.f : sum;
     int a = kbest < 0 ? kNoIndex : entry_v(kbest);
     lane_halves<16>(__float_as_uint(sum), lo, hi);
     sum = __uint_as_float(lo) + __uint_as_float(hi);

@@ -804,3 +804,43 @@ def test_draft_confidence_shares(asv, dev, V, sizes):
                workspace=ws)
     want = torch.softmax(q[torch.from_numpy(off[:-1]).long().to(dev)].double(), 1).max(1)[0]
     assert ((out.draft_conf - want).abs() / want).max() < 4e-6
+
+
+@pytest.mark.parametrize("tile", [0, 64, 128, 192, 256])
+def test_non_number_logits(asv, dev, tile):
+    """Logits that are no numbers or infinite (weights that hold them), on every tile: row_max and
+    row_argmax pass over non-numbers; one among other logits makes row_lse a non-number, but one that
+    is alone among its lane's entries of the row (the last id of V = 517: the first of its group of
+    four) adds nothing; -inf adds nothing; +inf is the maximum and leaves no row_lse."""
+    import torch
+    print(f"[non-numbers] tile={tile}", flush=True)
+    V, H, N = 517, 64, 8
+    g = torch.Generator().manual_seed(5)
+    hidden = torch.randn((N, H), generator=g).to(torch.bfloat16)
+    hidden[0::2, 0], hidden[1::2, 0] = 1.0, -1.0
+    off = torch.tensor([0, N], dtype=torch.int32, device=dev)
+    parent = torch.tensor([-1] + list(range(N - 1)), dtype=torch.int32, device=dev)
+    tok = torch.zeros(N, dtype=torch.int32, device=dev)
+    nan, inf = float("nan"), float("inf")
+    for kind, v, value in [("none", 0, 0.0), ("last", V - 1, nan), ("inside", 100, nan),
+                           ("whole", None, nan), ("inf", 300, inf), ("last inf", V - 1, inf)]:
+        w = torch.randn((V, H), generator=torch.Generator().manual_seed(6)).to(torch.bfloat16) * 0.2
+        if kind == "whole":
+            w[:] = nan
+        elif kind != "none":
+            w[v] = 0.0
+            w[v, 0] = value
+        z = hidden.double() @ w.double().T
+        number = torch.where(z.isnan(), -inf, z)
+        lse = torch.logsumexp(number, 1)
+        if kind == "inside":
+            lse[:] = nan
+        lse[number.max(1)[0] == inf] = nan
+        for weight in (w.to(dev), asv.pack_lm_head(w.to(dev))):
+            got = asv.verify(hidden.to(dev), weight, tok, parent, off,
+                             torch.full((1,), 0.2, device=dev), k1_tile=tile)
+            assert torch.allclose(got.row_max.cpu().double(), number.max(1)[0], rtol=0, atol=1e-4), kind
+            if kind != "whole":
+                assert torch.equal(got.row_argmax.cpu().long(), number.argmax(1)), kind
+            assert torch.allclose(got.row_lse.cpu().double(), lse, rtol=0, atol=1e-4,
+                                  equal_nan=True), (kind, got.row_lse, lse)
