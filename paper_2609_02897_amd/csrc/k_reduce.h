@@ -57,6 +57,7 @@ struct ConfShare {
     if (!mine) return;
     float m = kNegInf, s = 0.f;
     if (readable(a)) {
+      m = __builtin_nanf("");    // fmaxf takes the other one: stays when all entries are no numbers
 #pragma unroll
       for (int k = 0; k < kConfPerLane; ++k) {
         x[k] = lo + k * kWave + lane < hi ? x[k] : kNegInf;

@@ -844,3 +844,29 @@ def test_non_number_logits(asv, dev, tile):
                 assert torch.equal(got.row_argmax.cpu().long(), number.argmax(1)), kind
             assert torch.allclose(got.row_lse.cpu().double(), lse, rtol=0, atol=1e-4,
                                   equal_nan=True), (kind, got.row_lse, lse)
+
+
+@pytest.mark.parametrize("sizes", [(8,), (30, 35)])
+def test_draft_confidence_non_number(asv, dev, sizes):
+    """A draft logit that is no number leaves no confidence, alone or where all 32 entries that one
+    lane reduces are none (ids 5, 69, 133, ... of a record), in K1's tiles and in K4's own launch."""
+    import torch
+    print(f"[conf non-number] sizes={sizes}", flush=True)
+    V, H, N, B = 5000, 64, sum(sizes), len(sizes)
+    g = torch.Generator(device=dev)
+    g.manual_seed(N)
+    w = torch.empty((V, H), dtype=torch.bfloat16, device=dev).normal_(0, 0.1, generator=g)
+    hidden = torch.empty((N, H), dtype=torch.bfloat16, device=dev).normal_(0, 1, generator=g)
+    off = np.cumsum((0,) + sizes).astype(np.int32)
+    parent = np.concatenate([np.r_[-1, lo + np.arange(n - 1) // 2]
+                             for lo, n in zip(off, sizes)]).astype(np.int32)
+    args = (torch.zeros(N, dtype=torch.int32, device=dev), torch.from_numpy(parent).to(dev),
+            torch.from_numpy(off).to(dev), torch.full((B,), 0.2, device=dev))
+    for ids in ([], [3000], list(range(2048 + 5, 4096, 64))):
+        q = torch.empty((N, V), device=dev).normal_(0, 2, generator=g)
+        want = torch.softmax(q[args[2][:-1].long()].double(), 1).max(1)[0]
+        q[0, ids] = float("nan")
+        out = asv.verify(hidden, w, *args, q, state=asv.state_init(B, device=dev))
+        assert bool(out.draft_conf[0].isnan()) == bool(ids), ids
+        rest = slice(1 if ids else 0, B)
+        assert ((out.draft_conf - want).abs() / want)[rest].le(4e-6).all()
