@@ -240,7 +240,8 @@ typedef struct asv_draft_args {
 } asv_draft_args;
 
 /* Workspace asv_draft_step needs (per-vocabulary-slab top-4 records); 256-byte aligned, no
- * initialisation needed. Returns ASV_EINVAL for sizes asv_draft_step would reject. */
+ * initialisation needed; never falls as B or V grow, so that the largest batch's serves every
+ * smaller one. Returns ASV_EINVAL for sizes asv_draft_step would reject. */
 int asv_draft_workspace_bytes(int32_t B, int32_t H, int32_t V, uint64_t *bytes);
 
 /* The packed draft LM-head weight: the same idea as asv_pack_lm_head with [64][64] tiles, since
@@ -343,7 +344,8 @@ const char *asv_last_error(void);
 /* Device workspace that asv_verify needs for these sizes (partial per-vocab-slab records of
  * the LM-head kernel and draft-confidence partials). Writes the byte count to *bytes. The
  * workspace must be 256-byte aligned; its contents need no initialisation and are
- * overwritten by every call. Returns ASV_EINVAL for sizes asv_verify would reject. */
+ * overwritten by every call. The count never falls as B, N or V grow: a workspace for the largest
+ * batch serves every smaller one. Returns ASV_EINVAL for sizes asv_verify would reject. */
 int asv_workspace_bytes(int32_t B, int32_t N, int32_t H, int32_t V, uint64_t *bytes);
 
 /* Tree shape for the next draft (Sec. 3.3, Eq. (2)). For each request b: if conf is not NULL,

@@ -180,6 +180,12 @@ constexpr int kMinCut = 32;
 // small part of the launch, and their records stay as few as they were.
 constexpr int kMaxCutVocab = 1 << 18;
 
+// Most slabs of the cut up to 64 rows: one per 64 ids, or fewer than one per CU of 256. It grows
+// with V, and the draft head's records at 64 rows need no more workspace than 64-id slabs did.
+int max_records64(int V) {
+  return std::max((V + 63) / 64, std::min((V + kMinCut - 1) / kMinCut, 256));
+}
+
 Cut64 cut_rows64(int V, int cus) {
   // ids per slab when n slabs share `ids`, in whole groups of 8
   auto share = [](int ids, int n) { return std::max(kMinCut, ((ids + n - 1) / n + 7) / 8 * 8); };
@@ -187,18 +193,22 @@ Cut64 cut_rows64(int V, int cus) {
     const int S = (V + width - 1) / width;
     return Cut64{kind, SlabCut{S, width, width, 0, 0}, S, false};
   };
+  auto bounded = [&](const Cut64& c) {
+    return c.S <= max_records64(V) ? c : even(Stream64::kWide256, kSlab);
+  };
   if (V > kMaxCutVocab) return even(Stream64::kWide256, kSlab);
   const int one = share(V, cus), two = share(V, 2 * cus);
-  if (one <= 128) return even(Stream64::kDeep128, one);
+  if (one <= 128) return bounded(even(Stream64::kDeep128, one));
   // one workgroup per CU is 4-7% ahead of two half as wide at 150-200 ids (V = 40000: 57 against
   // 62 us, 50000: 68-70 against 71-73) and 2% behind at 250 (V = 64000: 85 against 83)
   if (one <= 224) return even(Stream64::kSpread256, one);
-  if (two <= 128) return even(Stream64::kDeep128, two);
+  if (two <= 128) return bounded(even(Stream64::kDeep128, two));
   if (two <= 256) return even(Stream64::kWide256, two);
   const int n1 = V / (2 * cus * 128) * 2 * cus, rest = V - n1 * 128;
   const bool tail64 = rest <= 2 * cus * 64;
   const int tw = tail64 ? 64 : share(rest, 2 * cus);
-  return Cut64{Stream64::kDeep128, SlabCut{n1, 128, tw, 0, 0}, n1 + (rest + tw - 1) / tw, tail64};
+  return bounded(
+      Cut64{Stream64::kDeep128, SlabCut{n1, 128, tw, 0, 0}, n1 + (rest + tw - 1) / tw, tail64});
 }
 
 // ---- The cut of the vocabulary from 65 to 512 rows. A last round that 256-id slabs leave partly
@@ -222,7 +232,7 @@ struct CutWide {
 
 constexpr int kMaxCutRows = 512;
 constexpr int kRows64Cost = 44;     // a round of 256 ids x 64 rows behind others, in the plan's units
-constexpr int kMaxCutTail = 512;    // most slabs of a tail (the workspace holds as many records)
+constexpr int kMaxCutTail = 256;    // most slabs of a tail (the workspace holds as many records)
 
 CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
   CutWide best;
@@ -270,11 +280,17 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
   return best;
 }
 
-// Most records per row that a step of N rows writes, whatever the device's CU count.
-int max_records(int N, int V) {
-  const int whole = (V + kSlab - 1) / kSlab;
-  if (N > kMaxCutRows || V > kMaxCutVocab) return whole;
-  return N <= 64 ? (V + kMinCut - 1) / kMinCut : whole + kMaxCutTail;
+// Most records that a step of up to N rows writes, whatever the device's CU count: the largest of
+// what the three ranges of rows may write, so that it never falls as N or V grow and a workspace
+// sized for the largest batch serves every smaller one.
+size_t max_records(int N, int V) {
+  const size_t whole = (V + kSlab - 1) / kSlab;
+  const int cut_V = std::min(V, kMaxCutVocab);       // no cut beyond it
+  size_t n = std::max((size_t)N * whole, (size_t)std::min(N, 64) * max_records64(cut_V));
+  if (N > 64)
+    n = std::max(n, (size_t)std::min(N, kMaxCutRows) *
+                        ((cut_V + kSlab - 1) / kSlab + kMaxCutTail));
+  return n;
 }
 
 // Launches of at most this many row tiles copy W with the non-temporal hint (the one or two
@@ -340,7 +356,7 @@ Layout layout(int B, int N, int V) {
   Layout L;
   L.S = (V + kSlab - 1) / kSlab;
   L.n_conf = (V + kConfChunk - 1) / kConfChunk;
-  const size_t rec = (size_t)N * max_records(N, V) * 4;
+  const size_t rec = max_records(N, V) * 4;
   const size_t conf = (size_t)B * L.n_conf * 4;
   size_t at = 0;
   L.off_rec_m = at;  at += align_up(rec);
@@ -592,16 +608,17 @@ struct DraftLayout {
   size_t off_k = 0, off_s = 0, bytes = 0;
 };
 
-// Most records per draft row, whatever the device's CU count.
-int max_draft_records(int R, int V) {
-  const int width = R > 64 ? 128 : V <= kMaxCutVocab ? kMinCut : kSlab;
-  return (V + width - 1) / width;
+// Most records that a draft step of up to R rows writes, whatever the device's CU count: never
+// falling as R or V grow (see max_records).
+size_t max_draft_records(int R, int V) {
+  const size_t n = (size_t)std::min(R, 64) * max_records64(V);
+  return R <= 64 ? n : std::max(n, (size_t)R * ((V + 127) / 128));
 }
 
 DraftLayout draft_layout(int B, int V) {
   DraftLayout L;
   const int R = B * kTopK;
-  const size_t rec = (size_t)R * max_draft_records(R, V);
+  const size_t rec = max_draft_records(R, V);
   size_t at = 0;
   L.off_k = at; at += align_up(rec * kTopK * 8);
   L.off_s = at; at += align_up(rec * 4);

@@ -91,6 +91,39 @@ def test_workspace_bytes(lib):
     assert lib.asv_workspace_bytes(1, 4, 64, 10, None) == asv.ASV_EINVAL
 
 
+def _bytes(fn, *args):
+    out = ctypes.c_uint64(0)
+    assert fn(*args, ctypes.byref(out)) == 0, args
+    return out.value
+
+
+def test_workspace_of_the_largest_batch_serves_every_smaller_one(lib):
+    """The workspace sizes never fall as the rows, the requests or the vocabulary grow: across the
+    row counts where the LM head's cut of the vocabulary changes, and across its own lines."""
+    verify, draft = lib.asv_workspace_bytes, lib.asv_draft_workspace_bytes
+    vocab = sorted([4, 100, 8191, 8192, 8193, 16384, 16385, 32000, 65536, 65537, 128256, 131073,
+                    151936, 200000, 1 << 18, (1 << 18) + 1, 300000, 1 << 20])
+    for V in vocab:
+        sizes = [_bytes(verify, 1, N, 64, V) for N in
+                 [1, 2, 30, *range(60, 70), 100, *range(500, 520), 600, 1000, 3048]]
+        assert sizes == sorted(sizes), V
+        sizes = [_bytes(verify, B, 600, 64, V) for B in (1, 2, 17, 64, 600)]
+        assert sizes == sorted(sizes), V
+        sizes = [_bytes(draft, B, 64, V) for B in range(1, 70)]
+        assert sizes == sorted(sizes), V
+    for N in (1, 8, 64, 65, 190, 512, 513, 3048):
+        sizes = [_bytes(verify, 1, N, 64, V) for V in vocab]
+        assert sizes == sorted(sizes), N
+    for B in (1, 16, 17, 32, 64):
+        sizes = [_bytes(draft, B, 64, V) for V in vocab]
+        assert sizes == sorted(sizes), B
+    # one draft buffer for 32 requests at 32000 ids: 500 records of 36 bytes at 64 rows
+    assert _bytes(draft, 16, 4096, 32000) == _bytes(draft, 32, 4096, 32000) == 1152000
+    # what the static scratch of asv_verify_noalloc took with 256-id slabs it still takes
+    for N, V in ((64, 1 << 23), (100, 6_900_000), (512, 1 << 20), (4500, 151936)):
+        assert 12 * N * (V // 256) < 32 << 20 and _bytes(verify, 1, N, 64, V) <= 32 << 20, (N, V)
+
+
 def test_verify_rejects_on_host(lib):
     """Every rejection below happens before any HIP call, so it runs without a GPU."""
     a = _abi.AsvVerifyArgs()

@@ -870,3 +870,28 @@ def test_draft_confidence_non_number(asv, dev, sizes):
         assert bool(out.draft_conf[0].isnan()) == bool(ids), ids
         rest = slice(1 if ids else 0, B)
         assert ((out.draft_conf - want).abs() / want)[rest].le(4e-6).all()
+
+
+@pytest.mark.parametrize("V", [5000, 32000, 151936])
+def test_one_workspace_for_smaller_batches(asv, dev, V):
+    """One workspace, sized for 600 rows, serves 400, 190 and 60 rows: each call's results are those
+    of a call with a workspace of its own."""
+    import torch
+    print(f"[one workspace] V={V}", flush=True)
+    H, B = 64, 4
+    g = torch.Generator(device=dev)
+    g.manual_seed(V)
+    w = torch.empty((V, H), dtype=torch.bfloat16, device=dev).normal_(0, 0.1, generator=g)
+    hidden = torch.empty((600, H), dtype=torch.bfloat16, device=dev).normal_(0, 1, generator=g)
+    tok = torch.randint(0, V, (600,), dtype=torch.int32, device=dev, generator=g)
+    ws = asv.alloc_workspace(B, 600, H, V, dev)
+    for N in (600, 400, 190, 60):
+        off = np.array([0, N // 4, N // 2, N - 5, N], np.int32)
+        parent = np.concatenate([np.r_[-1, lo + np.arange(hi - lo - 1) // 2]
+                                 for lo, hi in zip(off, off[1:])]).astype(np.int32)
+        args = (hidden[:N], w, tok[:N], torch.from_numpy(parent).to(dev),
+                torch.from_numpy(off).to(dev), torch.full((B,), 0.2, device=dev))
+        ws.fill_(0x7f)
+        got, own = asv.verify(*args, workspace=ws), asv.verify(*args)
+        for f in ("row_max", "row_lse", "row_argmax", "accept", "accepted_path", "bonus_token"):
+            assert torch.equal(getattr(got, f), getattr(own, f)), (N, f)
