@@ -388,30 +388,49 @@ typedef struct asv_tuning {
 int asv_verify_tuned(const asv_verify_args *args, const asv_tuning *tuning, void *workspace,
                      uint64_t workspace_bytes, void *stream);
 
-/* One launch of the LM-head kernel of asv_verify (see asv_k1_plan). Up to 64 rows the launch cuts
- * its ids anew into narrower slabs, by V and the compute units (cut_rows64 in asv_api.hip), and up
- * to 512 rows one launch with a tail of narrower slabs takes the place of the plan's where that is
- * estimated to be faster (cut_wide); the fields then describe the uncut 256-id slabs. */
+/* One launch of the plan of the LM-head kernel of asv_verify (see asv_k1_plan). */
 typedef struct asv_k1_launch {
   int32_t tile_rows;              /* tree rows per workgroup tile: 64, 128, 192 or 256 */
   int32_t slab0;                  /* first vocabulary slab (256 ids each) of the launch */
   int32_t n_slabs;                /* slabs it covers */
   int32_t row_tiles;              /* tiles along the tree rows: ceil(N / tile_rows) */
-  int32_t k_loop;                 /* 2 two-slot spread loop, 3 three-slot spread loop; for
-                                     64-row tiles 0, or 1 when the tiles fit three workgroups
-                                     per compute unit but not two */
+  int32_t k_loop;                 /* 0 burst ring (64-row tiles), 2 two-slot spread loop, 3
+                                     three-slot spread loop */
   int32_t stream_w;               /* 1: the weight is copied with the non-temporal hint */
   int32_t blk_slabs, blk_rows;    /* tile order: blocks of blk_slabs slabs x blk_rows row
                                      tiles, or 0 and 0 for the slab-major order */
 } asv_k1_launch;
 
-/* The LM-head launches asv_verify (asv_verify_tuned with tile_rows forced, 0 = the library's
- * choice) enqueues for N tree rows and V vocabulary ids on a GPU with `cus` compute units:
- * fills launches[0 .. *n_launches), at most two, in launch order. Host computation only; no
- * GPU call. ASV_EINVAL for N < 1, V < 1, N and V beyond asv_verify_args' bound, cus < 1, a
- * tile_rows asv_tuning rejects or null pointers. */
+/* The plan of the LM-head launches of asv_verify (asv_verify_tuned with tile_rows forced, 0 = the
+ * library's choice) over whole slabs of 256 ids, for N tree rows and V vocabulary ids on a GPU
+ * with `cus` compute units: fills launches[0 .. *n_launches), at most two, in launch order. They
+ * are the launches that are enqueued wherever asv_k1_cut reports no cut; where it reports one, a
+ * single launch over that cut takes their place. Host computation only; no GPU call. ASV_EINVAL
+ * for N < 1, V < 1, N and V beyond asv_verify_args' bound, cus < 1, a tile_rows asv_tuning
+ * rejects or null pointers. */
 int asv_k1_plan(int32_t N, int32_t V, int32_t cus, int32_t tile_rows, asv_k1_launch *launches,
                 int32_t *n_launches);
+
+/* One launch of an LM-head kernel over slabs of other widths: main_slabs slabs of main_ids ids
+ * each from id 0 on, then tail_slabs of tail_ids ids each up to the last id (the last slab may be
+ * shorter). A slab runs on workgroup tiles of main_tile_ids ids x main_tile_rows rows (in the
+ * tail: tail_tile_ids x tail_tile_rows), as many as its rows take, and writes one record per
+ * row. A part without slabs is all zeros. */
+typedef struct asv_lmhead_cut {
+  int32_t main_slabs, main_ids, main_tile_ids, main_tile_rows;
+  int32_t tail_slabs, tail_ids, tail_tile_ids, tail_tile_rows;
+  int32_t records;                /* per row: main_slabs + tail_slabs */
+} asv_lmhead_cut;
+
+/* The cut that asv_verify launches in place of asv_k1_plan's launches (always up to 64 rows on the
+ * 64-row tile, up to 512 rows where it is estimated to be faster), or records = 0 where those run
+ * as they are. Arguments and errors as asv_k1_plan. */
+int asv_k1_cut(int32_t N, int32_t V, int32_t cus, int32_t tile_rows, asv_lmhead_cut *cut);
+
+/* The cut that asv_draft_step launches for B >= 1 requests (4B draft rows) and V draft ids on a GPU
+ * with `cus` compute units. Host computation only; ASV_EINVAL for sizes asv_draft_step would
+ * reject, cus < 1 or a null pointer. */
+int asv_draft_cut(int32_t B, int32_t V, int32_t cus, asv_lmhead_cut *cut);
 int asv_draft_step_tuned(const asv_draft_args *args, const asv_tuning *tuning, void *workspace,
                          uint64_t workspace_bytes, void *stream);
 

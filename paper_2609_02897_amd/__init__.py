@@ -304,15 +304,37 @@ def verify(hidden, w_lm, draft_tok, parent, req_offsets, tau, draft_logits=None,
 
 
 def k1_plan(N: int, V: int, cus: int, tile_rows: int = 0) -> list:
-    """The LM-head launches ``verify`` enqueues for N tree rows and V vocabulary ids on a GPU
-    with ``cus`` compute units (``k1_tile`` = tile_rows; 0 = the library's choice), as dicts
-    in launch order. Host computation only (``asv_k1_plan``)."""
+    """The plan of ``verify``'s LM-head launches over whole 256-id slabs, for N tree rows and V
+    vocabulary ids on a GPU with ``cus`` compute units (``k1_tile`` = tile_rows; 0 = the library's
+    choice), as dicts in launch order; they run where ``k1_cut`` gives None. Host computation only
+    (``asv_k1_plan``)."""
     lib = load()
     out = (_abi.AsvK1Launch * 2)()
     n = ctypes.c_int32(0)
     _check(lib.asv_k1_plan(N, V, cus, tile_rows, out, ctypes.byref(n)))
     return [{f: getattr(out[i], f) for f, _ in _abi.AsvK1Launch._fields_}
             for i in range(n.value)]
+
+
+def _cut(cut) -> Optional[dict]:
+    return {f: getattr(cut, f) for f, _ in cut._fields_} if cut.records else None
+
+
+def k1_cut(N: int, V: int, cus: int, tile_rows: int = 0) -> Optional[dict]:
+    """The cut of the vocabulary that one launch of ``verify``'s LM head runs in place of
+    ``k1_plan``'s launches, as a dict, or None where those run. Host computation only
+    (``asv_k1_cut``)."""
+    out = _abi.AsvLmheadCut()
+    _check(load().asv_k1_cut(N, V, cus, tile_rows, ctypes.byref(out)))
+    return _cut(out)
+
+
+def draft_cut(B: int, V: int, cus: int) -> dict:
+    """The cut of the draft vocabulary that ``draft_step``'s LM head runs for B requests. Host
+    computation only (``asv_draft_cut``)."""
+    out = _abi.AsvLmheadCut()
+    _check(load().asv_draft_cut(B, V, cus, ctypes.byref(out)))
+    return _cut(out)
 
 
 def _tuning(events=None, tile_rows: int = 0) -> AsvTuning:

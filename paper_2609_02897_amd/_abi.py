@@ -23,7 +23,7 @@ EXPORTS = ("asv_version", "asv_status_string", "asv_last_error", "asv_workspace_
            "asv_draft_step", "asv_draft_prune", "asv_tree_meta", "asv_commit",
            "asv_packed_lm_head_bytes", "asv_pack_lm_head", "asv_packed_draft_head_bytes",
            "asv_pack_draft_head", "asv_verify_tuned", "asv_draft_step_tuned",
-           "asv_verify_noalloc", "asv_k1_plan")
+           "asv_verify_noalloc", "asv_k1_plan", "asv_k1_cut", "asv_draft_cut")
 
 
 class AsvReqState(ctypes.Structure):
@@ -66,6 +66,12 @@ class AsvK1Launch(ctypes.Structure):
                 ("n_slabs", ctypes.c_int32), ("row_tiles", ctypes.c_int32),
                 ("k_loop", ctypes.c_int32), ("stream_w", ctypes.c_int32),
                 ("blk_slabs", ctypes.c_int32), ("blk_rows", ctypes.c_int32)]
+
+
+class AsvLmheadCut(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in
+                ("main_slabs", "main_ids", "main_tile_ids", "main_tile_rows", "tail_slabs",
+                 "tail_ids", "tail_tile_ids", "tail_tile_rows", "records")]
 
 
 class AsvDraftTree(ctypes.Structure):
@@ -148,6 +154,10 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.asv_k1_plan.restype = ctypes.c_int
     lib.asv_k1_plan.argtypes = [ctypes.c_int32] * 4 + [ctypes.POINTER(AsvK1Launch),
                                                        ctypes.POINTER(ctypes.c_int32)]
+    lib.asv_k1_cut.restype = ctypes.c_int
+    lib.asv_k1_cut.argtypes = [ctypes.c_int32] * 4 + [ctypes.POINTER(AsvLmheadCut)]
+    lib.asv_draft_cut.restype = ctypes.c_int
+    lib.asv_draft_cut.argtypes = [ctypes.c_int32] * 3 + [ctypes.POINTER(AsvLmheadCut)]
     lib.asv_draft_step_tuned.restype = ctypes.c_int
     lib.asv_draft_step_tuned.argtypes = [ctypes.POINTER(AsvDraftArgs),
                                          ctypes.POINTER(AsvTuning), _P, ctypes.c_uint64, _P]

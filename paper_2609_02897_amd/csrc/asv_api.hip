@@ -141,10 +141,6 @@ void tile_blocking(int RT, int cus, int* blk_slabs, int* blk_rows) {
   }
 }
 
-// Whether a launch of `tiles` 64-row tiles fits three workgroups per CU but not two (the plan's
-// k_loop; up to 64 rows cut_rows64 decides what runs).
-bool three_per_cu_64(int tiles, int cus) { return tiles > 2 * cus && tiles <= 3 * cus; }
-
 // ---- The cut of the vocabulary up to 64 rows, where K1 streams W once and nothing else counts.
 // 256-id slabs leave the chip short of work when there are few of them, and a short last round
 // when they do not divide among the CUs: V = 32000 gave 125 workgroups, V = 151936 two rounds of
@@ -309,8 +305,8 @@ int tile_rows_of(Tile t) {
   }
 }
 
-// The K1 launches of a verification step over N rows and S slabs on `cus` CUs: the plan's one
-// or two launches, each with its K loop, W copy policy and tile order. Returns the count.
+// The K1 launches of the plan over N rows and S whole slabs on `cus` CUs, one or two, each with its
+// K loop, W copy policy and tile order. Returns the count.
 int k1_launches(int N, int S, int cus, const K1Plan& plan, asv_k1_launch out[2]) {
   int n = 0;
   auto add = [&](Tile t, int slab0, int n_slabs) {
@@ -319,9 +315,8 @@ int k1_launches(int N, int S, int cus, const K1Plan& plan, asv_k1_launch out[2])
     k.slab0 = slab0;
     k.n_slabs = n_slabs;
     k.row_tiles = (N + k.tile_rows - 1) / k.tile_rows;
-    const int tiles = n_slabs * k.row_tiles;
     switch (t) {
-      case Tile::kRows64: k.k_loop = three_per_cu_64(tiles, cus) ? 1 : 0; break;
+      case Tile::kRows64: k.k_loop = 0; break;
       case Tile::kRows128: k.k_loop = 3; break;
       default: k.k_loop = 2; break;
     }
@@ -342,6 +337,59 @@ bool forced_tile(int rows, Tile* t) {
     case 256: *t = Tile::kRows256; return true;
     default: return false;
   }
+}
+
+// What K1 runs in a step of N rows: one launch over a cut of the vocabulary up to 64 rows (cut64)
+// or, up to 512, where it is estimated to be faster (wide); else the plan's launches.
+struct K1Step {
+  asv_k1_launch plan[2];
+  int n_plan;
+  bool rows64;
+  Cut64 cut64;
+  CutWide wide;
+  int S;           // records per row
+};
+
+// tile: the forced one, or null for the library's choice.
+K1Step k1_step(int N, int V, int cus, const Tile* tile) {
+  K1Step st{};
+  st.S = (V + kSlab - 1) / kSlab;
+  int64_t est = 0;           // no cut beyond 64 rows where the tile is forced
+  const K1Plan plan = tile ? K1Plan{*tile, *tile, st.S} : plan_k1(N, st.S, cus, &est);
+  st.n_plan = k1_launches(N, st.S, cus, plan, st.plan);
+  st.rows64 = N <= 64 && plan.a == Tile::kRows64;
+  if (st.rows64) {
+    st.cut64 = cut_rows64(V, cus);
+    st.S = st.cut64.S;
+  } else {
+    st.wide = cut_wide(N, V, cus, est);
+    if (st.wide.rows) st.S = st.wide.S;
+  }
+  return st;
+}
+
+int tile_ids_of(Stream64 kind) { return kind == Stream64::kDeep128 ? 128 : kSlab; }
+
+// A cut as asv_lmhead_cut describes it.
+asv_lmhead_cut describe(const SlabCut& c, int S, int ids, int rows, int tail_ids, int tail_rows) {
+  asv_lmhead_cut r{};
+  r.records = S;
+  if (c.n_main > 0) {
+    r.main_slabs = c.n_main;
+    r.main_ids = c.width;
+    r.main_tile_ids = ids;
+    r.main_tile_rows = rows;
+  }
+  if (S > c.n_main) {
+    r.tail_slabs = S - c.n_main;
+    r.tail_ids = c.tail_width;
+    r.tail_tile_ids = tail_ids;
+    r.tail_tile_rows = tail_rows;
+  }
+  return r;
+}
+asv_lmhead_cut describe(const Cut64& c, int ids, int rows) {
+  return describe(c.cut, c.S, ids, rows, c.tail64 ? 64 : ids, rows);
 }
 
 struct Layout {
@@ -769,17 +817,11 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   const bool conf = a->draft_logits != nullptr;
   (void)hipGetLastError();
 
-  const int cus = cu_count();
-  int64_t est = 0;           // no cut where the tile is forced
-  const K1Plan plan = tu.tile_rows != 0 ? K1Plan{forced, forced, L.S}
-                                         : plan_k1(a->N, L.S, cus, &est);
-  const CutWide wide = cut_wide(a->N, a->V, cus, est);
-  asv_k1_launch k1[2];
-  const int n_k1 = k1_launches(a->N, L.S, cus, plan, k1);
-  const bool rows64 = k1[0].tile_rows == 64 && a->N <= 64;
-  const Cut64 cut64 = cut_rows64(a->V, cus);
-  const int S = rows64 ? cut64.S : wide.rows ? wide.S : L.S;             // records per row
-  LmheadArgs g = lmhead_args(a, L, ws, S);
+  const K1Step step = k1_step(a->N, a->V, cu_count(), tu.tile_rows != 0 ? &forced : nullptr);
+  const Cut64& cut64 = step.cut64;
+  const CutWide& wide = step.wide;
+  const bool rows64 = step.rows64;
+  LmheadArgs g = lmhead_args(a, L, ws, step.S);
   // K4 only needs the inputs: up to 64 rows its shares go to K1's tiles, one each, which saves its
   // launch (8 rows at V = 128256, one request: 165.6 -> 162.9 us), where there are enough tiles
   g.conf = ConfArgs{a->N, a->V, a->req_offsets, a->draft_logits,
@@ -803,9 +845,9 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
     case 256: launch_cut_rows<256, 2>(g, wide, s, K1Events{ev_begin, ev_end}); break;
     default: break;
   }
-  for (int q = 0; q < n_k1 && !wide.rows; ++q) {
-    const asv_k1_launch& k = k1[q];
-    const K1Events ev{q == 0 ? ev_begin : nullptr, q == n_k1 - 1 ? ev_end : nullptr};
+  for (int q = 0; q < step.n_plan && !wide.rows; ++q) {
+    const asv_k1_launch& k = step.plan[q];
+    const K1Events ev{q == 0 ? ev_begin : nullptr, q == step.n_plan - 1 ? ev_end : nullptr};
     // <tree rows, waves along vocab, waves along rows, ring depth, K loop>, each the fastest of
     // a sweep on MI355X for its row range. The 128-, 192- and 256-row tiles run the spread K
     // loops (copies spaced between the MFMAs), in interleaved comparisons 28% faster than the
@@ -831,27 +873,59 @@ extern "C" int asv_verify_tuned(const asv_verify_args* a, const asv_tuning* tuni
   int32_t* cnt = reinterpret_cast<int32_t*>(ws + L.off_cnt);
   if (a->B <= kFusedMaxB) {
     k_merge_accept<<<(a->N + kFinishWaves - 1) / kFinishWaves, kFinishWaves * kWave, 0, s>>>(
-        S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, cnt, acc);
+        step.S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, cnt, acc);
     return launch_status("k_merge_accept");
   }
   k_slab_merge<<<(a->N + kMergeRowsPerBlock - 1) / kMergeRowsPerBlock,
                  kMergeRowsPerBlock * kWave, 0, s>>>(
-      a->N, S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, a->B,
+      a->N, step.S, rec_m, rec_s, rec_a, a->row_max, a->row_lse, a->row_argmax, a->B,
       a->req_offsets, cnt + a->B);
   if (int rc = launch_status("k_slab_merge")) return rc;
   k_tree_accept<<<a->B, kWave, 0, s>>>(cnt + a->B, acc);
   return launch_status("k_tree_accept");
 }
 
-extern "C" int asv_k1_plan(int32_t N, int32_t V, int32_t cus, int32_t tile_rows,
-                           asv_k1_launch* launches, int32_t* n_launches) {
-  if (N < 1 || V < 1 || cus < 1 || !grid_ok(N, V) || !launches || !n_launches)
-    return ASV_EINVAL;
+// The step of asv_k1_plan and asv_k1_cut; ASV_EINVAL for sizes asv_verify would reject.
+static int checked_step(int N, int V, int cus, int tile_rows, K1Step* step) {
+  if (N < 1 || V < 1 || cus < 1 || !grid_ok(N, V)) return ASV_EINVAL;
   Tile forced = Tile::kRows64;
   if (tile_rows != 0 && !forced_tile(tile_rows, &forced)) return ASV_EINVAL;
-  const int S = (V + kSlab - 1) / kSlab;
-  const K1Plan plan = tile_rows != 0 ? K1Plan{forced, forced, S} : plan_k1(N, S, cus);
-  *n_launches = k1_launches(N, S, cus, plan, launches);
+  *step = k1_step(N, V, cus, tile_rows != 0 ? &forced : nullptr);
+  return ASV_OK;
+}
+
+extern "C" int asv_k1_plan(int32_t N, int32_t V, int32_t cus, int32_t tile_rows,
+                           asv_k1_launch* launches, int32_t* n_launches) {
+  K1Step step;
+  if (!launches || !n_launches) return ASV_EINVAL;
+  if (int rc = checked_step(N, V, cus, tile_rows, &step)) return rc;
+  for (int q = 0; q < step.n_plan; ++q) launches[q] = step.plan[q];
+  *n_launches = step.n_plan;
+  return ASV_OK;
+}
+
+extern "C" int asv_k1_cut(int32_t N, int32_t V, int32_t cus, int32_t tile_rows,
+                          asv_lmhead_cut* cut) {
+  K1Step step;
+  if (!cut) return ASV_EINVAL;
+  if (int rc = checked_step(N, V, cus, tile_rows, &step)) return rc;
+  const CutWide& w = step.wide;
+  *cut = step.rows64 ? describe(step.cut64, tile_ids_of(step.cut64.kind), 64)
+         : w.rows    ? describe(w.cut, w.S, kSlab, w.rows, w.tail_ids, w.tail_rows)
+                     : asv_lmhead_cut{};
+  return ASV_OK;
+}
+
+extern "C" int asv_draft_cut(int32_t B, int32_t V, int32_t cus, asv_lmhead_cut* cut) {
+  if (B < 1 || cus < 1 || !cut || !draft_sizes_ok(B, kKAlign, V)) return ASV_EINVAL;
+  const DraftPlan p = plan_draft(B * kTopK, V, cus);
+  switch (p.tile) {
+    case DraftTile::kRows64: *cut = describe(p.cut, tile_ids_of(p.cut.kind), 64); break;
+    case DraftTile::kRows128x128: *cut = describe(p.cut, 128, 128); break;
+    case DraftTile::kRows128x192: *cut = describe(p.cut, 192, 128); break;
+    case DraftTile::kRows128x256: *cut = describe(p.cut, 256, 128); break;
+    case DraftTile::kRows256x128: *cut = describe(p.cut, 128, 256); break;
+  }
   return ASV_OK;
 }
 

@@ -241,17 +241,18 @@ def test_blocked_tile_order(asv, dev):
 
 @pytest.mark.parametrize("V,sizes,tile", [(140000, (30, 21, 4), 0),
                                           (80000, (40, 33, 27), 64)])
-def test_one_slot_weight_stream(asv, dev, V, sizes, tile):
-    """When a launch's 64-row tiles fit three per CU but not two (on a 256-CU GPU: 513-768
-    tiles) the 64-row tile runs its one-slot ring: V = 140000 (547 slabs, one row tile) with
-    the library's pick, and V = 80000 (313 slabs, two row tiles at 100 rows) with the 64-row
-    tile forced. The records, drafted logits and walks match the oracle, and the other tile
-    families bit for bit."""
-    assert asv.k1_plan(sum(sizes), V, 256, tile)[0]["k_loop"] == 1
-    print(f"[one-slot ring] V={V} N={sum(sizes)} tile={tile}", flush=True)
+def test_weight_stream_tiles(asv, dev, V, sizes, tile):
+    """64-row tiles that stream the weight: V = 140000 at 55 rows with the library's pick (two rounds
+    of 128-id slabs and a tail, on 256 CUs), and V = 80000 at 100 rows with the 64-row tile forced
+    (256-id slabs, two row tiles). The records, drafted logits and walks match the oracle, and the
+    other tile families bit for bit."""
+    assert asv.k1_plan(sum(sizes), V, 256, tile)[0]["tile_rows"] == 64
+    cut = asv.k1_cut(sum(sizes), V, 256, tile)
+    assert cut is None if tile else (cut["main_slabs"], cut["main_ids"]) == (1024, 128)
+    print(f"[weight stream] V={V} N={sum(sizes)} tile={tile}", flush=True)
     rng = np.random.default_rng(V)
     trees = [_rand_tree(rng, n, 6, 4) for n in sizes]
-    w = custom_workload(f"one_slot{V}", 256, V, trees, 0.2, seed=18, w_std=0.1,
+    w = custom_workload(f"weight_stream{V}", 256, V, trees, 0.2, seed=18, w_std=0.1,
                         draft_logits=True)
     W = w.weights()
     w64 = oracle.widen_weights(W)
@@ -260,7 +261,7 @@ def test_one_slot_weight_stream(asv, dev, V, sizes, tile):
     runs = {}
     for rows, packed in ((tile, True), (tile, False), (128, True), (256, True)):
         runs[(rows, packed)] = _run(asv, w, W, dev, k1_tile=rows, packed=packed)
-        compare(w, ref, runs[(rows, packed)], tag=f"one-slot tile={rows} packed={packed}")
+        compare(w, ref, runs[(rows, packed)], tag=f"weight stream tile={rows} packed={packed}")
     base = runs[(tile, True)]
     nonroot = w.parent >= 0
     for key, got in runs.items():
