@@ -614,10 +614,14 @@ AcceptArgs accept_args(const asv_verify_args* a, const Layout& L, char* ws, bool
 // ---- draft side
 
 // The draft LM head (K5) by draft rows R = 4B. Up to 64 rows it streams its weight like K1 and
-// runs K1's cut and tiles (cut_rows64). Beyond, one workgroup per CU: an equal share of the ids
-// where that fits a tile of 128, 192 or 256 ids (128 rows) or 128 ids (256 rows), else the rounds
-// of the cheapest of these tiles.
-enum class DraftTile { kRows64, kRows128x128, kRows128x192, kRows128x256, kRows256x128 };
+// runs K1's cut and tiles (cut_rows64), except where the vocabulary leaves each CU one slab of 64
+// ids: those run on a 64-id tile of 32 or 64 rows, which holds nothing that it doesn't read and
+// fills its ring three stages ahead instead of two. Beyond, one workgroup per CU: an equal share of
+// the ids where that fits a tile of 128, 192 or 256 ids (128 rows) or 128 ids (256 rows), else the
+// rounds of the cheapest of these tiles.
+enum class DraftTile {
+  kRows32x64, kRows64x64, kRows64, kRows128x128, kRows128x192, kRows128x256, kRows256x128
+};
 
 struct DraftPlan {
   DraftTile tile;
@@ -626,7 +630,20 @@ struct DraftPlan {
 };
 
 DraftPlan plan_draft(int R, int V, int cus) {
-  if (R <= 64) return DraftPlan{DraftTile::kRows64, cut_rows64(V, cus), 1};
+  auto slabs = [&](DraftTile tile, int width, int row_tiles) {
+    const int S = (V + width - 1) / width;
+    return DraftPlan{tile, Cut64{Stream64::kDeep128, SlabCut{S, width, width, 0, 0}, S, false},
+                     row_tiles};
+  };
+  if (R <= 64) {
+    // Whole draft steps at H = 4096, K1's cut against the 64-id tile: V = 16384 36.2 against 27.4 us
+    // at 1 request, 39.2 against 30.8 at 16. Past one slab per CU some CUs run two: from 16640 ids
+    // on 39.3 against 46.7 us at 16 requests, 36.4 against 37.5 at 4, but 36.5 against 35.1 at 1
+    // and 36.3 against 35.9 at 2; 22000 ids are level there.
+    if (V <= (int64_t)cus * (R <= 8 ? 80 : 64))
+      return slabs(R <= 32 ? DraftTile::kRows32x64 : DraftTile::kRows64x64, 64, 1);
+    return DraftPlan{DraftTile::kRows64, cut_rows64(V, cus), 1};
+  }
   struct Family { DraftTile tile; int ids, rows, cost; };
   // cost of one round of tiles, in us at H = 4096 (MI355X)
   const Family families[4] = {{DraftTile::kRows128x128, 128, 128, 46},
@@ -642,12 +659,10 @@ DraftPlan plan_draft(int R, int V, int cus) {
     if (est >= best_est) continue;
     best_est = est;
     // the slabs one round's row tiles leave room for, ids shared equally
-    const int64_t slabs = std::max<int64_t>(1, rounds * cus / RT);
+    const int64_t n = std::max<int64_t>(1, rounds * cus / RT);
     const int width = (int)std::min<int64_t>(
-        f.ids, std::max<int64_t>(128, ((V + slabs - 1) / slabs + 7) / 8 * 8));
-    const int S = (V + width - 1) / width;
-    best = DraftPlan{f.tile, Cut64{Stream64::kDeep128, SlabCut{S, width, width, 0, 0}, S, false},
-                     RT};
+        f.ids, std::max<int64_t>(128, ((V + n - 1) / n + 7) / 8 * 8));
+    best = slabs(f.tile, width, RT);
   }
   return best;
 }
@@ -920,6 +935,8 @@ extern "C" int asv_draft_cut(int32_t B, int32_t V, int32_t cus, asv_lmhead_cut* 
   if (B < 1 || cus < 1 || !cut || !draft_sizes_ok(B, kKAlign, V)) return ASV_EINVAL;
   const DraftPlan p = plan_draft(B * kTopK, V, cus);
   switch (p.tile) {
+    case DraftTile::kRows32x64: *cut = describe(p.cut, 64, 32); break;
+    case DraftTile::kRows64x64: *cut = describe(p.cut, 64, 64); break;
     case DraftTile::kRows64: *cut = describe(p.cut, tile_ids_of(p.cut.kind), 64); break;
     case DraftTile::kRows128x128: *cut = describe(p.cut, 128, 128); break;
     case DraftTile::kRows128x192: *cut = describe(p.cut, 192, 128); break;
@@ -1009,6 +1026,12 @@ extern "C" int asv_draft_step_tuned(const asv_draft_args* a, const asv_tuning* t
                     reinterpret_cast<hipEvent_t>(tu.end_event)};
   const DraftPlan p = plan_draft(a->B * kTopK, a->V, cu_count());
   switch (p.tile) {
+    case DraftTile::kRows32x64:
+      launch_draft<TileFamily<64, 32, 2, 1, 4, 0, true, Mfma32>>(a, L, ws, p, s, ev);
+      break;
+    case DraftTile::kRows64x64:
+      launch_draft<TileFamily<64, 64, 2, 2, 4, 0, true, Mfma32>>(a, L, ws, p, s, ev);
+      break;
     case DraftTile::kRows64:
       switch (p.cut.kind) {
         case Stream64::kDeep128:

@@ -650,12 +650,14 @@ def test_many_requests(asv, dev):
 
 
 # Sizes on either side of every line of the draft LM head's plan (on 256 CUs): up to 64 rows the
-# vocabulary's cut, beyond it one round of 128-, 192- and 256-id tiles (the row tile's remainders
-# among them), the rounds of the cheapest one, and two row tiles of 256.
-@pytest.mark.parametrize("B,V", [(1, 4), (1, 8193), (16, 32769), (9, 57345), (16, 65537), (5, 131073),
-                                 (2, 163841), (3, 262145), (17, 4), (17, 32768), (32, 32769),
-                                 (20, 49153), (32, 65537), (32, 98305), (33, 32768), (64, 32769),
-                                 (65, 5000)])
+# 64-id tiles of 32 and 64 rows, then the vocabulary's cut, beyond it one round of 128-, 192- and
+# 256-id tiles (the row tile's remainders among them), the rounds of the cheapest one, and two row
+# tiles of 256.
+@pytest.mark.parametrize("B,V", [(1, 4), (1, 8193), (8, 16384), (9, 16384), (16, 65), (16, 16385),
+                                 (2, 20480), (2, 20481), (3, 16385), (16, 32769), (9, 57345),
+                                 (16, 65537), (5, 131073), (2, 163841), (3, 262145), (17, 4),
+                                 (17, 32768), (32, 32769), (20, 49153), (32, 65537), (32, 98305),
+                                 (33, 32768), (64, 32769), (65, 5000)])
 def test_draft_plan_edges(asv, dev, B, V):
     """Top-4, log-probabilities and row_lse against float64 for each tile and cut, both weight
     layouts. H = 64: float32 sums of 64 products of bf16 values with |z| < 16 are within 64 * 16 *

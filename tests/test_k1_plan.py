@@ -118,6 +118,10 @@ def test_documented_cuts(N, V, expected):
 
 
 @pytest.mark.parametrize("B,V,expected", [
+    # one 64-id slab a CU (and a few more at one or two requests): tiles that hold no more
+    (1, 16000, _cut((250, 64, 64, 32))), (8, 5000, _cut((79, 64, 64, 32))),
+    (9, 16384, _cut((256, 64, 64, 64))), (2, 20480, _cut((320, 64, 64, 32))),
+    (3, 16385, _cut((228, 72, 128, 64))), (2, 20481, _cut((233, 88, 128, 64))),
     (1, 32000, _cut((250, 128, 128, 64))), (16, 48000, _cut((250, 192, 256, 64))),
     (17, 32000, _cut((250, 128, 128, 128))), (32, 48000, _cut((250, 192, 192, 128))),
     (32, 64000, _cut((250, 256, 256, 128))), (40, 32000, _cut((250, 128, 128, 256))),
