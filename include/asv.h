@@ -244,9 +244,8 @@ typedef struct asv_draft_args {
  * smaller one. Returns ASV_EINVAL for sizes asv_draft_step would reject. */
 int asv_draft_workspace_bytes(int32_t B, int32_t H, int32_t V, uint64_t *bytes);
 
-/* The packed draft LM-head weight: the same idea as asv_pack_lm_head with [64][64] tiles, since
- * the draft LM-head kernel reads slabs of 64 or 128 vocabulary rows. With Vp = V rounded up to
- * a multiple of 128 and T = Vp / 64 tiles per 64-column block:
+/* The packed draft LM-head weight: asv_pack_lm_head's layout for fewer rows, in [64][64] tiles.
+ * With Vp = V rounded up to a multiple of 128 and T = Vp / 64 tiles per 64-column block:
  *   packed[((k * T + s) * 64 + r) * 64 + c] = w[64 s + r][64 k + c], zero where 64 s + r >= V.
  * It holds Vp * H bf16 values. asv_packed_draft_head_bytes returns ASV_EINVAL for sizes
  * asv_draft_step would reject or a copy of 4 GiB or more; asv_pack_draft_head takes the same

@@ -211,10 +211,13 @@ Cut64 cut_rows64(int V, int cus) {
 // empty costs as much as a full one, and the plan's second family (more row tiles on the remaining
 // slabs) a second launch and another pass over those slabs. Here the slabs fill whole rounds of
 // one family, and the ids that remain are shared equally among the CUs, one narrower tile each, in
-// the same launch. Behind two rounds and more the tail's slabs stay 256 ids wide, on 64-row tiles
-// (they share each W slab through an XCD's L2): level with the narrower slabs there (190 rows at
-// V = 151936, with the policy 254 -> 250 us), and the records, and with them row_lse, are the plan's
-// bit for bit.
+// the same launch. Behind two rounds and more the tail's slabs stay 256 ids wide, on 64-row tiles:
+// the records, and with them row_lse, are then the plan's bit for bit. That costs time at 65 to 128
+// rows: narrower tails there took K1 from 209-214 to 188-194 us (100 and 128 rows, V = 140000, after
+// a flush of the last-level cache), 1-7% less at 150 to 256 rows. The tail keeps the non-temporal
+// hint although its two to eight row tiles read each W slab through an XCD's L2: after a flush, as a
+// target forward leaves it, K1 takes 252 us with it and 266 without (190 rows, V = 151936; 3-8%
+// at 65 to 256 rows), in back-to-back calls 265 and 247.
 // Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
 // V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 213; 190 rows at 32000 71 -> 61, 81920
 // 149 -> 134, 147456 242 -> 233; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 36864
@@ -239,7 +242,7 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
   // rounds: 30-34, 38-46 and 52-60 us (128 rows), 32-41, 50-55 and 70-71, 42-52, 57-64 and 85-87
   const Family families[3] = {{128, 62, {{64, 30}, {128, 44}, {192, 60}}},
                               {192, 80, {{64, 36}, {128, 54}, {192, 70}}},
-                              {256, 98, {{64, 44}, {128, 70}, {192, 90}}}};
+                              {256, 98, {{64, 44}, {192, 90}, {0, 0}}}};    // its 128-id tail never wins
   int64_t best_est = plan_est;
   for (const Family& f : families) {
     const int RT = (N + f.rows - 1) / f.rows, per_round = cus / RT;    // slabs of one round
@@ -251,7 +254,10 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
       const int n_tail = (rest + width - 1) / width;
       int64_t est = (int64_t)rounds * f.cost + t.cost;
       // two row tiles: level with the plan where the estimates are within 6% (378 rows at
-      // V = 49152 136 against 134 us, 500 rows at 81920 275 against 265)
+      // V = 49152 136 against 134 us, 500 rows at 81920 275 against 265). Where the plan is three
+      // 128-row tiles and the weight stays in the last-level cache, back-to-back steps are up to 12%
+      // slower (300 rows, V = 40960, H = 2560 82 against 93 us); after a flush K1 is 20-40% faster
+      // (98 against 76 us)
       if (RT == 2) est = est * 53 / 50;
       if (rounds > 1 || rest == 0 || width > t.ids || n_tail > kMaxCutTail || est >= best_est)
         continue;
@@ -548,7 +554,9 @@ void launch_cut_rows(const LmheadArgs& g, const CutWide& c, hipStream_t s, const
   }
   switch (c.tail_ids) {
     case 64: launch_cut<TR, NST, 64, 3>(g, c, s, ev); break;
-    case 128: launch_cut<TR, NST, 128, 3>(g, c, s, ev); break;
+    case 128:
+      if constexpr (TR != 256) launch_cut<TR, NST, 128, 3>(g, c, s, ev);
+      break;
     // three slots of 192 ids and 256 rows are 168 KB
     default: launch_cut<TR, NST, 192, TR == 256 ? 2 : 3>(g, c, s, ev); break;
   }
@@ -694,11 +702,11 @@ bool draft_sizes_ok(int B, int H, int V) {
   if (H % kKAlign != 0 || H > (1 << 20)) return false;
   // 32-bit offsets inside a tile's buffer resource: all 4B rows of X and one slab of W
   if ((int64_t)B * kTopK * H * 2 >= (int64_t)1 << 31) return false;
-  // the draft LM head's workgroup count stays an int
-  const int R = B * kTopK;
-  const int tv = R <= 64 ? 64 : 128, tr = R <= 32 ? 32 : R <= 64 ? 64 : 128;
-  const int64_t S = ((int64_t)V + tv - 1) / tv;
-  return S * (((int64_t)R + tr - 1) / tr) < ((int64_t)1 << 31);
+  // the draft LM head's workgroup count stays an int: at most ceil(V / 64) slabs up to 64 rows
+  // (or one per CU of a small V), ceil(V / 128) slabs of 128-row tiles beyond
+  const int64_t R = (int64_t)B * kTopK, ids = R <= 64 ? 64 : 128;
+  const int64_t row_tiles = R <= 64 ? 1 : (R + 127) / 128;
+  return (V + ids - 1) / ids * row_tiles < ((int64_t)1 << 31);
 }
 
 template <class M, class T = M>
