@@ -33,26 +33,54 @@ static int check(const char* name, int rows_total, int wave_rows) {
   return reads;
 }
 
+// Every fragment read of tile family F: W of TV ids in the waves' ranges of ids, X of TR rows in
+// theirs, in the layout of its MFMA shape.
+template <class F>
+static int check_family(const char* name) {
+  using C = typename F::C;
+  using MF = typename F::MF;
+  const int w = check<C::CPR, MF::kBlock, MF::kK>(name, F::TV, C::kWaveV);
+  const int x = check<C::CPR, MF::kBlock, MF::kK>(name, F::TR, C::kWaveR);
+  return w < 0 || x < 0 ? -1 : w + x;
+}
+
 int main() {
+  using asv::Mfma16;
+  using asv::Mfma32;
+  using asv::TileFamily;
   int total = 0, r;
-  // K1, v_mfma_f32_16x16x32_bf16 (kBlock 16, kK 32), 128-byte rows (BK 64):
-  // W regions of 256 rows read in 64-row (4 waves) or 128-row (2 waves) wave ranges,
-  // X regions of 64, 128, 192 and 256 rows in 64-, 64-, 96- and 128-row wave ranges
-  if ((r = check<8, 16, 32>("K1 W 64-row waves", 256, 64)) < 0) return 1; total += r;
-  if ((r = check<8, 16, 32>("K1 W 128-row waves", 256, 128)) < 0) return 1; total += r;
-  if ((r = check<8, 16, 32>("K1 X 64 rows", 64, 64)) < 0) return 1; total += r;
-  if ((r = check<8, 16, 32>("K1 X 128 rows", 128, 64)) < 0) return 1; total += r;
-  if ((r = check<8, 16, 32>("K1 X 192 rows", 192, 96)) < 0) return 1; total += r;
-  if ((r = check<8, 16, 32>("K1 X 256 rows", 256, 128)) < 0) return 1; total += r;
-  // K5, v_mfma_f32_32x32x16_bf16 (kBlock 32, kK 16), 128-byte rows: W of 64 or 128 rows in
-  // 32- or 64-row wave ranges, X of 32, 64 or 128 rows in 32-row wave ranges
-  if ((r = check<8, 32, 16>("K5 W 64 rows", 64, 32)) < 0) return 1; total += r;
-  if ((r = check<8, 32, 16>("K5 W 128 rows", 128, 64)) < 0) return 1; total += r;
-  if ((r = check<8, 32, 16>("K5 X 32 rows", 32, 32)) < 0) return 1; total += r;
-  if ((r = check<8, 32, 16>("K5 X 64 rows", 64, 32)) < 0) return 1; total += r;
-  if ((r = check<8, 32, 16>("K5 X 128 rows", 128, 32)) < 0) return 1; total += r;
-  // 64-byte rows (BK 32, 32x32x16 only)
-  if ((r = check<4, 32, 16>("64-byte rows", 128, 32)) < 0) return 1; total += r;
+#define FAMILY(...)                                                          \
+  if ((r = check_family<TileFamily<__VA_ARGS__>>(#__VA_ARGS__)) < 0) return 1; \
+  total += r;
+  // <ids, rows, waves along ids, waves along rows, ring depth, K loop, W hint, MFMA shape>
+  // whole 256-id slabs
+  FAMILY(256, 64, 4, 1, 2, 0, true)
+  FAMILY(256, 128, 2, 2, 3, 3, true)
+  FAMILY(256, 192, 2, 2, 2, 2, true)
+  FAMILY(256, 256, 2, 2, 2, 2, true)
+  // the cuts up to 64 rows (K1 and K5)
+  FAMILY(128, 64, 4, 1, 3, 0, true)
+  FAMILY(64, 64, 4, 1, 4, 0, true)
+  FAMILY(256, 64, 2, 2, 3, 3, true)
+  // the tails of the cuts up to 512 rows
+  FAMILY(64, 128, 2, 2, 3, 3, true)
+  FAMILY(128, 128, 2, 2, 3, 3, true)
+  FAMILY(192, 128, 2, 2, 3, 3, true)
+  FAMILY(64, 192, 2, 2, 3, 3, true)
+  FAMILY(128, 192, 2, 2, 3, 3, true)
+  FAMILY(192, 192, 2, 2, 3, 3, true)
+  FAMILY(64, 256, 2, 2, 3, 3, true)
+  FAMILY(192, 256, 2, 2, 2, 2, true)
+  // K5: small vocabularies, and beyond 64 rows
+  FAMILY(64, 32, 2, 1, 4, 0, true, Mfma32)
+  FAMILY(64, 64, 2, 2, 4, 0, true, Mfma32)
+  FAMILY(128, 128, 2, 4, 3, 0, false, Mfma32)
+  FAMILY(192, 128, 2, 4, 3, 3, true)
+  FAMILY(256, 128, 2, 4, 3, 3, true)
+  FAMILY(128, 256, 2, 4, 3, 3, true)
+  // 64-byte rows (32-deep stages, 32x32x16 only)
+  if ((r = check<4, 32, 16>("64-byte rows", 128, 32)) < 0) return 1;
+  total += r;
   std::printf("ok %d\n", total);
   return 0;
 }

@@ -295,14 +295,20 @@ def test_long_hidden_16384(asv, dev):
         compare(w, ref, got, tag=f"long hidden tile={rows} packed={packed}")
 
 
-@pytest.mark.parametrize("N", [150, 200, 378])
+@pytest.mark.parametrize("N", [150, 200, 300, 378])
 def test_two_family_plan(asv, dev, N):
     """At V = 151936 and these row counts the library splits the vocabulary slabs between two
-    LM-head tile families in two launches (on 256 CUs: 128-row tiles on the first slabs, 192-
-    or 256-row tiles on the rest), so that no round of workgroups runs a third empty. Every
-    output equals the single-family runs' bit for bit (the same K order everywhere, and both
+    LM-head tile families: in two launches (on 256 CUs: 128-row tiles on the first slabs, 192-
+    or 256-row tiles on the rest), so that no round of workgroups runs a third empty, or at 150
+    rows in one launch of 192-row tiles with a tail of 64-row tiles. Every output equals the
+    single-family runs' bit for bit (the same K order and the same slabs everywhere, and all
     families merge a slab's record across two waves), and the oracle's."""
     print(f"[two families] N={N}", flush=True)
+    cut, plan = asv.k1_cut(N, 151936, 256), asv.k1_plan(N, 151936, 256)
+    if N == 150:
+        assert (cut["main_tile_rows"], cut["tail_tile_rows"], cut["tail_ids"]) == (192, 64, 256)
+    else:
+        assert cut is None and len(plan) == 2 and plan[0]["tile_rows"] == 128
     rng = np.random.default_rng(N)
     trees, n = [], 0
     while n < N:
@@ -695,6 +701,20 @@ def test_empty_batch(asv, dev):
     assert o.accepted_len.numel() == 0
 
 
+def _check_rows(got, hidden, w):
+    """row_max, row_argmax and row_lse against float64. Float32 sums of H <= 128 products with
+    |partial sums| < 8 are within 128 * 8 * 2^-24 = 6.1e-5; a row_lse moves by no more than its
+    logits, and by a few 1e-6 for its own sum."""
+    import torch
+    for n in range(0, hidden.shape[0], 64):
+        z = hidden[n:n + 64].double() @ w.double().T
+        top, rows = z.topk(2, dim=1)[0], slice(n, n + z.shape[0])
+        assert (got.row_max[rows] - top[:, 0]).abs().max() < 1e-4
+        clear = top[:, 0] - top[:, 1] > 2e-4
+        assert torch.equal(got.row_argmax[rows][clear].long(), z.argmax(1)[clear])
+        assert (got.row_lse[rows] - torch.logsumexp(z, 1)).abs().max() < 1e-4
+
+
 # Vocabularies on either side of every line of the cut that K1 makes up to 64 rows (on 256 CUs):
 # the narrowest slabs, one and two workgroups per CU at 128 and 224-256 ids, whole rounds with a
 # tail of 64-id slabs, of wider ones and of one id, and uncut 256-id slabs.
@@ -703,7 +723,7 @@ def test_empty_batch(asv, dev):
 @pytest.mark.parametrize("sizes", [(1,), (30, 21, 13)])
 def test_rows64_vocabulary_cut(asv, dev, V, sizes):
     """Up to 64 rows the vocabulary is cut into slabs by its size and the CU count. Against the
-    general path (the 128-row tile forced: 256-id slabs), on both weight layouts: the logits and
+    general path (the 128-row tile forced: 256-id slabs) and float64, on both weight layouts: the logits and
     all that is decided from them bit for bit, row_lse up to the order its slab sums are added
     in (as in test_every_tile_same_results)."""
     import torch
@@ -722,6 +742,7 @@ def test_rows64_vocabulary_cut(asv, dev, V, sizes):
     args = (tok, torch.from_numpy(parent).to(dev), torch.from_numpy(off).to(dev),
             torch.full((B,), 0.2, device=dev))
     base = asv.verify(hidden, w, *args, k1_tile=128)
+    _check_rows(base, hidden, w)
     nonroot = torch.from_numpy(parent >= 0).to(dev)
     ws = asv.alloc_workspace(B, N, H, V, dev)
     for weight in (w, asv.pack_lm_head(w)):
@@ -732,22 +753,40 @@ def test_rows64_vocabulary_cut(asv, dev, V, sizes):
             assert torch.equal(getattr(got, f), getattr(base, f)), f
         assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
         assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
+        _check_rows(got, hidden, w)
 
 
-# From 65 to 512 rows: the smallest V of each (row tile, tail width) on 256 CUs, alone and behind
-# whole rounds of 256-id slabs, ends of the row tiles, and sizes that keep the plan's slabs.
-@pytest.mark.parametrize("N,V", [(65, 5), (65, 16385), (128, 32769), (128, 65537), (100, 81921),
-                                 (120, 98305), (129, 16000), (192, 32768), (192, 65600), (150, 90000),
-                                 (192, 98305), (193, 16384), (256, 65536 + 16385), (193, 32769),
-                                 (256, 36864), (256, 40961), (300, 33000), (384, 57344),
-                                 (385, 34000), (512, 36864), (513, 34000), (70, 262145),
-                                 (90, 131072 + 255), (190, 151936), (256, 140000), (230, 65700)])
-def test_wide_vocabulary_cut(asv, dev, N, V):
+# From 65 to 512 rows: every (row tile, tail tile) that 256 CUs choose, at one row tile and at two,
+# alone and behind whole rounds of 256-id slabs, most at the smallest V or the ends of the row tiles;
+# a tail of one id; and sizes that keep the plan's slabs. cut: rows of the main slabs' tiles (0: none),
+# ids and rows of the tail's.
+@pytest.mark.parametrize("N,V,cut", [
+    (65, 5, (0, 64, 128)), (137, 256, (0, 64, 128)), (128, 16385, (0, 128, 128)),
+    (65, 16385, (0, 128, 128)), (128, 32769, (0, 192, 128)),
+    (129, 16000, (0, 64, 192)), (300, 8000, (0, 64, 192)), (192, 32768, (0, 128, 192)),
+    (263, 9141, (0, 128, 192)), (384, 16384, (0, 128, 192)), (137, 34019, (0, 192, 192)),
+    (257, 21761, (0, 192, 192)), (193, 16384, (0, 64, 256)), (389, 256, (0, 64, 256)),
+    (193, 32769, (0, 192, 256)), (256, 40961, (0, 192, 256)), (512, 22000, (0, 192, 256)),
+    (128, 65537, (128, 64, 128)), (100, 81921, (128, 128, 128)), (120, 98305, (128, 192, 128)),
+    (192, 65600, (192, 64, 192)), (300, 33000, (192, 64, 192)), (150, 90000, (192, 128, 192)),
+    (192, 98305, (192, 192, 192)), (384, 57344, (192, 192, 192)),
+    (230, 65700, (256, 64, 256)), (389, 39350, (256, 64, 256)), (512, 40960, (256, 64, 256)),
+    (200, 99768, (256, 192, 256)),
+    (90, 131072 + 1, (128, 256, 64)), (90, 131072 + 255, (128, 256, 64)),
+    (190, 151936, (192, 256, 64)), (263, 76667, (192, 256, 64)), (256, 140000, (256, 256, 64)),
+    (389, 66005, (256, 256, 64)),
+    (256, 81921, None), (385, 34000, None), (512, 36864, None), (513, 34000, None),
+    (70, 262145, None)])
+def test_wide_vocabulary_cut(asv, dev, N, V, cut):
     """From 65 to 512 rows the ids beyond whole rounds go to one tail of narrower slabs or, behind
-    two rounds, of 64-row tiles. Against
-    the plan's whole slabs (a forced tile), on both weight layouts, as in the test above."""
+    two rounds, of 64-row tiles. Against the plan's whole slabs (a forced tile) and float64, on both
+    weight layouts, as in the test above."""
     import torch
     print(f"[wide cut] N={N} V={V}", flush=True)
+    c = asv.k1_cut(N, V, 256)
+    assert cut == (c and (c["main_tile_rows"], c["tail_tile_ids"], c["tail_tile_rows"]))
+    if torch.cuda.get_device_properties(dev).multi_processor_count != 256:
+        pytest.skip("the cuts are those of 256 CUs")
     H = 64
     g = torch.Generator(device=dev)
     g.manual_seed(V + N)
@@ -762,6 +801,7 @@ def test_wide_vocabulary_cut(asv, dev, N, V):
     args = (tok, torch.from_numpy(parent).to(dev), torch.from_numpy(off).to(dev),
             torch.full((3,), 0.2, device=dev))
     base = asv.verify(hidden, w, *args, k1_tile=128)
+    _check_rows(base, hidden, w)
     nonroot = torch.from_numpy(parent >= 0).to(dev)
     ws = asv.alloc_workspace(3, N, H, V, dev)
     for weight in (w, asv.pack_lm_head(w)):
@@ -772,6 +812,38 @@ def test_wide_vocabulary_cut(asv, dev, N, V):
             assert torch.equal(getattr(got, f), getattr(base, f)), f
         assert torch.equal(got.drafted_logit[nonroot], base.drafted_logit[nonroot])
         assert torch.allclose(got.row_lse, base.row_lse, rtol=1e-6, atol=1e-6)
+        _check_rows(got, hidden, w)
+
+
+@pytest.mark.parametrize("V,H,N", [(100000, 16384, 60), (50000, 32768, 64), (45000, 32768, 120)])
+def test_narrow_cut_past_2gib(asv, dev, V, H, N):
+    """Slabs of 200, 200 and 176 ids on tiles of 256, 256 and 192, of packed weights of 3.0 to 3.3 GB:
+    past 2 GiB the rows that a slab does not hold are really read, from the next slab, and must be
+    discarded. Against the row-major weight, whose reads end with the slab, bit for bit; the draft
+    head's 200-id slabs likewise."""
+    import torch
+    print(f"[cut past 2 GiB] V={V} H={H} N={N}", flush=True)
+    c = asv.k1_cut(N, V, 256)
+    ids, tile = (c[("main_" if c["main_slabs"] else "tail_") + f] for f in ("ids", "tile_ids"))
+    assert ids < tile and V * H * 2 > 2**31
+    g = torch.Generator(device=dev)
+    g.manual_seed(V)
+    bf = dict(dtype=torch.bfloat16, device=dev)
+    w = torch.empty((V, H), **bf).normal_(0, 0.01, generator=g)
+    hidden = torch.empty((N, H), **bf).normal_(0, 1, generator=g)
+    args = (torch.randint(0, V, (N,), dtype=torch.int32, device=dev, generator=g),
+            torch.arange(-1, N - 1, dtype=torch.int32, device=dev),
+            torch.tensor([0, N], dtype=torch.int32, device=dev), torch.full((1,), 0.2, device=dev))
+    ref, got = asv.verify(hidden, w, *args), asv.verify(hidden, asv.pack_lm_head(w), *args)
+    assert torch.isfinite(ref.row_lse).all()
+    for f in ("row_max", "row_lse", "row_argmax", "accept", "accepted_path", "bonus_token"):
+        assert torch.equal(getattr(got, f), getattr(ref, f)), f
+    assert torch.equal(got.drafted_logit[1:], ref.drafted_logit[1:])
+    if asv.draft_cut(2, V, 256)["main_ids"] == 200:
+        outs = [asv.draft_step(hidden[:8], weight, asv.alloc_draft_trees(2, dev), 0, shape=(3, 4, 4))
+                for weight in (w, asv.pack_draft_head(w))]
+        for f in ("topk_id", "topk_logp", "row_lse", "front_tok"):
+            assert torch.equal(getattr(outs[0], f), getattr(outs[1], f)), f
 
 
 # Draft logits in K1's tiles (up to 64 rows, while its slabs outnumber the 8192-logit shares) and in
