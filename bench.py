@@ -39,9 +39,9 @@ TABLES = os.path.join(ROOT, "tests", "golden")
 TRAFFIC = os.path.join(ROOT, "profiles", "k1_traffic.json")
 # the kernels and the host code that picks their tiles
 K1_SOURCES = [os.path.join(ROOT, "paper_2609_02897_amd", "csrc", f)
-              for f in ("k_lmhead.h", "k_common.h", "asv_api.hip")]
+              for f in ("k_lmhead.h", "k_reduce.h", "k_common.h", "asv_api.hip")]
 K5_SOURCES = [os.path.join(ROOT, "paper_2609_02897_amd", "csrc", f)
-              for f in ("k_draft.h", "k_lmhead.h", "k_common.h", "asv_api.hip")]
+              for f in ("k_draft.h", "k_lmhead.h", "k_reduce.h", "k_common.h", "asv_api.hip")]
 
 
 def _code_text(path) -> str:

@@ -22,8 +22,8 @@ namespace {
 
 constexpr size_t kAlign = 256;
 
-// Vocabulary slabs of K1's plan. A launch beyond 64 rows runs one workgroup tile and writes one
-// record per slab and row; up to 64 rows the slabs are cut anew (cut_rows64).
+// Vocabulary slabs of K1's plan, one workgroup tile and one record per slab and row. Up to 64 rows
+// the ids are cut anew (cut_rows64), up to 512 where that pays (cut_wide).
 constexpr int kSlab = 256;
 constexpr int kPackRowsTarget = 256;   // rows per tile of the packed target LM-head weight
 constexpr int kPackRowsDraft = 64;     // rows per tile of the packed draft LM-head weight
@@ -295,11 +295,11 @@ size_t max_records(int N, int V) {
   return n;
 }
 
-// Launches of at most this many row tiles copy W with the non-temporal hint (the one or two
-// tiles of a slab read it about once); more row tiles share each W slab through an XCD's L2
+// The plan's launches of at most this many row tiles copy W with the non-temporal hint (the one or
+// two tiles of a slab read it about once); more row tiles share each W slab through an XCD's L2
 // and keep the default policy. Against the earlier rule (the hint for tiles of up to 128 rows)
 // in same-box A/Bs: 260, 300, 378 and 450 rows 3% faster, 150 rows 1.4%, 500 rows 1%; 128,
-// 200 and 600 to 3048 rows level.
+// 200 and 600 to 3048 rows level. The cuts always copy with the hint.
 constexpr int kStreamWMaxRowTiles = 2;
 
 int tile_rows_of(Tile t) {
@@ -334,7 +334,7 @@ int k1_launches(int N, int S, int cus, const K1Plan& plan, asv_k1_launch out[2])
   return n;
 }
 
-// The tile asv_verify_args.k1_tile_rows asks for; false for a value that names no tile.
+// The tile that asv_tuning.tile_rows asks for; false for a value that names no tile.
 bool forced_tile(int rows, Tile* t) {
   switch (rows) {
     case 64: *t = Tile::kRows64; return true;

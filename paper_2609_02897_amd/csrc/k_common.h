@@ -29,7 +29,9 @@ __device__ __forceinline__ float exp2_rel(float x) { return __builtin_amdgcn_exp
 
 // The largest of two and of five floats, a non-number being the lowest: the compiler first brings
 // every operand of fmaxf into canonical form, an instruction more for each value that comes out of
-// a matrix instruction.
+// a matrix instruction. The compiler counts no wait states between a matrix instruction and inline
+// asm that reads its result: call these well behind the last one (K1's K loops end with a workgroup
+// barrier and LDS round trips, tens of cycles longer than the 19 that the slowest would need).
 __device__ __forceinline__ float max_raw(float a, float b) {
   float r;
   asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));

@@ -19,9 +19,9 @@
 // v_mfma_f32_16x16x32_bf16 with A = W (16 vocabulary rows) and B = X (16 tree rows): each lane
 // then owns one tree row and 4 vocabulary entries of every 16x16 output block, so the per-row
 // reduction is mostly lane-local, with two cross-lane steps. The draft LM head runs the same
-// tiles with an epilogue of its own (one of them on v_mfma_f32_32x32x16_bf16: 16 entries of a
-// 32x32 block per lane; the two shapes give the same logits bit for bit). Fragments of a later K step are read while the current MFMAs
-// run.
+// tiles with an epilogue of its own (three of them on v_mfma_f32_32x32x16_bf16: 16 entries of a
+// 32x32 block per lane; the two shapes give the same logits bit for bit). Fragments of a later K
+// step are read while the current MFMAs run.
 // Every loop accumulates K in increasing order, so all tiles give the same logits bit for bit.
 #pragma once
 
@@ -243,9 +243,10 @@ __host__ __device__ __forceinline__ void tile_coords(int t, int n_slabs, int RT,
 // the packed weight, whose rows past v_end belong to the next tile, their offset is set past any
 // buffer of up to 2 GiB (in a larger one those rows are read and discarded).
 // STREAM_W: copy W with the non-temporal hint. K1 takes it for launches of one or two row
-// tiles, which read each W slab about once (60 rows: 13% less time), and the default policy
-// for more row tiles, which share each W slab through an XCD's L2 (with the hint: 378 rows'
-// three 128-row tiles a slab about 2% slower, 2048 and 3048 rows 1.5% and 4.5%).
+// tiles, which read each W slab about once (60 rows: 13% less time), and for the cuts of up to 512
+// rows; the default policy for more row tiles over whole slabs, which share each W slab through an
+// XCD's L2 (with the hint: 378 rows' three 128-row tiles a slab about 2% slower, 2048 and 3048 rows
+// 1.5% and 4.5%).
 template <int TV, int TR, int WV, int WR, int BK, int NST, bool STREAM_W = (TR <= 128),
           class MF = Mfma16>
 struct TileIo {
