@@ -213,11 +213,12 @@ Cut64 cut_rows64(int V, int cus) {
 // one family, and the ids that remain are shared equally among the CUs, one narrower tile each, in
 // the same launch. Behind two rounds and more the tail's slabs stay 256 ids wide, on 64-row tiles:
 // the records, and with them row_lse, are then the plan's bit for bit. That costs time at 65 to 128
-// rows: narrower tails there took K1 from 209-214 to 188-194 us (100 and 128 rows, V = 140000, after
-// a flush of the last-level cache), 1-7% less at 150 to 256 rows. The tail keeps the non-temporal
-// hint although its two to eight row tiles read each W slab through an XCD's L2: after a flush, as a
-// target forward leaves it, K1 takes 252 us with it and 266 without (190 rows, V = 151936; 3-8%
-// at 65 to 256 rows), in back-to-back calls 265 and 247.
+// rows: narrower tails there took K1 from 205-211 to 189-195 us (100 and 128 rows, V = 140000, after
+// a read of 1 GiB), 1-7% less at 150 to 256 rows. The tail copies with the non-temporal hint,
+// although its two to eight row tiles read each W slab through an XCD's L2. Without it: 190 rows at
+// V = 151936 with the policy, on changing inputs, 257.5 -> 260.5 us; K1 alone 249 -> 244 us after a
+// read of 1 GiB (0-2% less at 65 to 256 rows) and 252 -> 266 after a fill of it, whose dirty lines
+// the copies without the hint push out; back-to-back steps 265 -> 247.
 // Whole verify steps at H = 4096, packed weight, before -> after: 120 rows at
 // V = 32000 68 -> 54 us, 73728 139 -> 120, 147456 222 -> 213; 190 rows at 32000 71 -> 61, 81920
 // 149 -> 134, 147456 242 -> 233; 250 rows at 40960 95 -> 85, 98304 179 -> 176; 378 rows at 36864
@@ -256,8 +257,8 @@ CutWide cut_wide(int N, int V, int cus, int64_t plan_est) {
       // two row tiles: level with the plan where the estimates are within 6% (378 rows at
       // V = 49152 136 against 134 us, 500 rows at 81920 275 against 265). Where the plan is three
       // 128-row tiles and the weight stays in the last-level cache, back-to-back steps are up to 12%
-      // slower (300 rows, V = 40960, H = 2560 82 against 93 us); after a flush K1 is 20-40% faster
-      // (98 against 76 us)
+      // slower (300 rows, V = 40960, H = 2560 82 against 93 us); after a read of 1 GiB, as a target
+      // forward leaves the cache, K1 is 1-9% faster (there 77 against 75 us)
       if (RT == 2) est = est * 53 / 50;
       if (rounds > 1 || rest == 0 || width > t.ids || n_tail > kMaxCutTail || est >= best_est)
         continue;
