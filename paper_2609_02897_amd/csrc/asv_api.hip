@@ -176,8 +176,8 @@ constexpr int kMinCut = 32;
 // small part of the launch, and their records stay as few as they were.
 constexpr int kMaxCutVocab = 1 << 18;
 
-// Most slabs of the cut up to 64 rows: one per 64 ids, or fewer than one per CU of 256. It grows
-// with V, and the draft head's records at 64 rows need no more workspace than 64-id slabs did.
+// Most slabs of the cut up to 64 rows: one per 64 ids, but up to 256 of them one per 32. It grows
+// with V, and from 16384 ids on the draft head needs no more workspace than 64-id slabs do.
 int max_records64(int V) {
   return std::max((V + 63) / 64, std::min((V + kMinCut - 1) / kMinCut, 256));
 }
